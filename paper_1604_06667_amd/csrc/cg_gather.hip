@@ -1,4 +1,5 @@
-// FP32 gather contraction, neighbour statistics and normalisation.
+// FP32 gather contraction of narrow data, neighbour statistics and
+// normalisation (wide data: cg_gather_wide.hip).
 //
 // Eq. (1)-(2): for every target t of a tile, S_t[c] += R_n[c] w and
 // W_t += w over the tile's candidate samples n with d <= r_s.  Each tile's
@@ -12,32 +13,6 @@
 namespace cg {
 
 constexpr int kChunk = 64;   // candidates staged per step
-
-__device__ __forceinline__ double wsum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// Target-frame axes for the elliptical kernel: east e = (-sin a, cos a, 0),
-// north n = (-sin d cos a, -sin d sin a, cos d); major axis along
-// cos(pa) n + sin(pa) e, minor axis along cos(pa) e - sin(pa) n.
-__device__ __forceinline__ void target_axes(const KernelParams& kp, double lon, double lat,
-                                            double* a, double* b) {
-  double sa, ca, sd, cd;
-  sincos(lon, &sa, &ca);
-  sincos(lat, &sd, &cd);
-  const double ex = -sa, ey = ca, ez = 0.0;
-  const double nx = -sd * ca, ny = -sd * sa, nz = cd;
-  a[0] = kp.cospa * nx + kp.sinpa * ex;
-  a[1] = kp.cospa * ny + kp.sinpa * ey;
-  a[2] = kp.cospa * nz + kp.sinpa * ez;
-  b[0] = kp.cospa * ex - kp.sinpa * nx;
-  b[1] = kp.cospa * ey - kp.sinpa * ny;
-  b[2] = kp.cospa * ez - kp.sinpa * nz;
-}
-
-__device__ __forceinline__ float qnan_f() { return __int_as_float(0x7fc00000); }
 
 // ---------------------------------------------------------------------------
 // Narrow data (nchan <= CMAX <= 16): one lane per target.  A chunk of
@@ -163,235 +138,6 @@ __global__ void __launch_bounds__(64) k_gather_tl(TileView tv, KernelParams kp,
   }
 }
 
-// ---------------------------------------------------------------------------
-// Wide data: 8 wavefronts x 8 targets per tile, lanes own VEC consecutive
-// channels of a 64*VEC channel block (grid.y).  A chunk of 64 candidates
-// and their data rows (read through the sort permutation) are staged in
-// LDS; for each target the lanes evaluate the 64 weights in parallel and the
-// wavefront then walks only the candidates inside the support.
-
-template <typename T>
-__device__ __forceinline__ float ld_f32(const T* p);
-template <>
-__device__ __forceinline__ float ld_f32<float>(const float* p) { return *p; }
-template <>
-__device__ __forceinline__ float ld_f32<double>(const double* p) { return (float)*p; }
-template <>
-__device__ __forceinline__ float ld_f32<uint16_t>(const uint16_t* p) {
-  return __uint_as_float(((uint32_t)*p) << 16);
-}
-template <>
-__device__ __forceinline__ float ld_f32<_Float16>(const _Float16* p) { return (float)*p; }
-
-template <int VEC, typename T>
-__device__ __forceinline__ void load_row_vec(const T* __restrict__ p, int nvalid, bool vec_ok,
-                                             float* out) {
-  if (vec_ok && nvalid >= VEC) {
-    if constexpr (sizeof(T) == 4 && VEC == 4) {
-      const float4 v = *reinterpret_cast<const float4*>(p);
-      out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
-      return;
-    } else if constexpr (sizeof(T) == 2 && VEC == 4) {
-      const uint2 v = *reinterpret_cast<const uint2*>(p);
-      const uint16_t h[4] = {(uint16_t)(v.x & 0xffff), (uint16_t)(v.x >> 16),
-                             (uint16_t)(v.y & 0xffff), (uint16_t)(v.y >> 16)};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) out[i] = ld_f32<T>(reinterpret_cast<const T*>(&h[i]));
-      return;
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < VEC; ++i) out[i] = (i < nvalid) ? ld_f32<T>(p + i) : 0.0f;
-}
-
-template <int VEC, int KT, typename T>
-__global__ void __launch_bounds__(512) k_gather_cl(TileView tv, KernelParams kp,
-                                                   const T* __restrict__ data, int64_t ld,
-                                                   int64_t nchan, int vec_ok_in, OutView ov) {
-  constexpr int CB = 64 * VEC;
-  constexpr int NWV = 8;    // wavefronts per workgroup
-  constexpr int TPW = kTile / NWV;   // targets per wavefront
-  __shared__ double s_x[kChunk], s_y[kChunk], s_z[kChunk];
-  __shared__ int64_t s_row[kChunk];
-  __shared__ __attribute__((aligned(16))) float s_d[kChunk * CB];
-  __shared__ double s_t[kTile][9];   // target xyz, major axis, minor axis
-  __shared__ double s_w[kTile];
-  int64_t tile, pass;
-  work_of_block(blockIdx.x, tv.ntiles, (nchan + CB - 1) / CB, &tile, &pass);
-  const int64_t c0 = pass * CB;
-  const int t = threadIdx.x, lane = t & 63, wv_id = t >> 6;
-  const int64_t ns = tv.nslots;
-  if (t < kTile) {
-    const int64_t slot = tile * kTile + t;
-    const double x = tv.txyz[slot];
-    s_t[t][0] = x;
-    s_t[t][1] = tv.txyz[ns + slot];
-    s_t[t][2] = tv.txyz[2 * ns + slot];
-    double a[3] = {0.0, 0.0, 0.0}, b[3] = {0.0, 0.0, 0.0};
-    if (KT == 1 && isfinite(x)) target_axes(kp, tv.tll[slot], tv.tll[ns + slot], a, b);
-    s_t[t][3] = a[0]; s_t[t][4] = a[1]; s_t[t][5] = a[2];
-    s_t[t][6] = b[0]; s_t[t][7] = b[1]; s_t[t][8] = b[2];
-  }
-  const int col = lane * VEC;
-  const int nvalid_c = (int)((nchan - c0 - col) < VEC ? (nchan - c0 - col) : VEC);
-  const bool vec_ok = vec_ok_in != 0;
-  double acc[TPW][VEC];
-  double wl[TPW];
-#pragma unroll
-  for (int i = 0; i < TPW; ++i) {
-    wl[i] = 0.0;
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) acc[i][v] = 0.0;
-  }
-  const uint32_t total = (uint32_t)tv.ntot[tile];
-  RangeWindow<false> rw;   // used by wavefront 0, which stages the candidates
-  if (wv_id == 0) rw.init(tv.rng + 2 * tv.roff[tile], tv.nr[tile], total, true);
-  for (uint32_t base = 0; base < total; base += kChunk) {
-    const int kmax = (int)(total - base < (uint32_t)kChunk ? total - base : (uint32_t)kChunk);
-    if (wv_id == 0) {
-      rw.cover(base, base + kmax - 1, true);
-      const int64_t pos = rw.pos(base + (t < kmax ? t : kmax - 1), base, base + kmax - 1);
-      if (t < kmax) {
-        const double4 r = tv.srec[pos];
-        s_x[t] = r.x;
-        s_y[t] = r.y;
-        s_z[t] = r.z;
-        s_row[t] = rec_row(r) * ld;
-      }
-    }
-    __syncthreads();
-    for (int r = wv_id; r < kmax; r += NWV) {
-      float v[VEC];
-      if (nvalid_c > 0) load_row_vec<VEC, T>(data + s_row[r] + c0 + col, nvalid_c, vec_ok, v);
-      else {
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) v[i] = 0.0f;
-      }
-#pragma unroll
-      for (int i = 0; i < VEC; ++i) s_d[r * CB + col + i] = v[i];
-    }
-    __syncthreads();
-    double cxv = 0.0, cyv = 0.0, czv = 0.0;
-    if (lane < kmax) { cxv = s_x[lane]; cyv = s_y[lane]; czv = s_z[lane]; }
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int tt = wv_id * TPW + i;
-      // keep the per-target LDS reads inside the loop (no hoisting of all 16 targets)
-      __asm__ volatile("" ::: "memory");
-      float w = 0.0f;
-      if (lane < kmax) {
-        const double dx = cxv - s_t[tt][0], dy = cyv - s_t[tt][1], dz = czv - s_t[tt][2];
-        const double c2 = dx * dx + dy * dy + dz * dz;
-        if (c2 <= kp.cs2) {
-          if (KT == 0)
-            w = exp2_neg(chord2_to_d2_for(kp, c2) * kp.k1);
-          else
-            w = pair_weight<KT == 3>(kp, c2, dx, dy, dz, s_t[tt][3], s_t[tt][4], s_t[tt][5], s_t[tt][6],
-                            s_t[tt][7], s_t[tt][8]);
-        }
-      }
-      wl[i] += (double)w;
-      uint64_t m = __ballot(w != 0.0f);
-      while (m) {
-        const int k = __ffsll((unsigned long long)m) - 1;
-        m &= m - 1;
-        const double wk = (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(w), k));
-        const float* dp = &s_d[k * CB + col];
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[i][v] = fma(wk, (double)dp[v], acc[i][v]);
-      }
-    }
-    __syncthreads();
-  }
-  // weight sums: lanes held one candidate each
-#pragma unroll
-  for (int i = 0; i < TPW; ++i) {
-    const double s = wsum(wl[i]);
-    if (lane == 0) s_w[wv_id * TPW + i] = s;
-  }
-  __syncthreads();
-  // transpose the tile's [target][channel] block through LDS (as FP64, in
-  // two halves of 32 targets): s_dd[c][target]
-  const bool fin = ov.mode == ACC_FINAL;
-  const bool tmaj = fin && ov.tst != 1;
-  double* s_dd = reinterpret_cast<double*>(s_d);
-  static_assert(sizeof(s_d) >= sizeof(double) * CB * (kTile / 2), "transpose buffer");
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    if (half) __syncthreads();
-#pragma unroll
-    for (int i = 0; i < TPW; ++i) {
-      const int tt = wv_id * TPW + i;
-      if ((tt >> 5) != half) continue;
-      const double wt = s_w[tt];
-#pragma unroll
-      for (int v = 0; v < VEC; ++v) {
-        double o;
-        if (fin) o = wt > 0.0 ? acc[i][v] / wt : (double)qnan_f();
-        else o = acc[i][v];
-        s_dd[(col + v) * (kTile / 2) + (tt & 31)] = o;
-      }
-    }
-    __syncthreads();
-    // consecutive threads write consecutive targets of a channel, or (target-
-    // major cubes) consecutive channels of a target
-    for (int idx = t; idx < CB * (kTile / 2); idx += 64 * NWV) {
-      const int c = tmaj ? idx % CB : idx / (kTile / 2);
-      const int l = tmaj ? idx / CB : idx % (kTile / 2);
-      if (c0 + c >= nchan) continue;
-      const int64_t slot = tile * kTile + half * (kTile / 2) + l;
-      const double o = s_dd[c * (kTile / 2) + l];
-      if (fin) {
-        const int32_t tg = ov.slot_target[slot];
-        if (tg >= 0) ov.cube[(c0 + c) * ov.cst + (int64_t)tg * ov.tst] = (float)o;
-      } else if (ov.mode == ACC_ADD) {
-        ov.S[(c0 + c) * ns + slot] += o;
-      } else {
-        ov.S[(c0 + c) * ns + slot] = o;
-      }
-    }
-  }
-  if (pass == 0 && t < kTile) {
-    const int64_t slot = tile * kTile + t;
-    if (fin) {
-      const int32_t tg = ov.slot_target[slot];
-      if (tg >= 0 && ov.wout) ov.wout[tg] = (float)s_w[t];
-    } else {
-      ov.W[slot] = ov.mode == ACC_ADD ? ov.W[slot] + s_w[t] : s_w[t];
-      ov.Wn[slot] = ov.mode == ACC_ADD ? ov.Wn[slot] + s_w[t] : s_w[t];
-    }
-  }
-}
-
-template <int VEC, typename T>
-static void launch_cl(const TileView& tv, const KernelParams& kp, const void* data, int64_t ld,
-                      int64_t nchan, const OutView& ov, hipStream_t st) {
-  const int64_t ncb = (nchan + 64 * VEC - 1) / (64 * VEC);
-  const dim3 g((unsigned)(tv.ntiles * ncb)), b(512);
-  // vector loads need every row start aligned to VEC elements
-  const int vec_ok = (ld % VEC == 0) && ((uintptr_t)data % (VEC * sizeof(T)) == 0) ? 1 : 0;
-  if (kp.type == 0)
-    hipLaunchKernelGGL((k_gather_cl<VEC, 0, T>), g, b, 0, st, tv, kp, (const T*)data, ld, nchan,
-                       vec_ok, ov);
-  else if (kp.type == 1)
-    hipLaunchKernelGGL((k_gather_cl<VEC, 1, T>), g, b, 0, st, tv, kp, (const T*)data, ld, nchan,
-                       vec_ok, ov);
-  else
-    hipLaunchKernelGGL((k_gather_cl<VEC, 3, T>), g, b, 0, st, tv, kp, (const T*)data, ld, nchan,
-                       vec_ok, ov);
-}
-
-template <int VEC>
-static void launch_cl_dt(const TileView& tv, const KernelParams& kp, const void* data, int dtype,
-                         int64_t ld, int64_t nchan, const OutView& ov, hipStream_t st) {
-  switch (dtype) {
-    case 0: launch_cl<VEC, double>(tv, kp, data, ld, nchan, ov, st); break;
-    case 1: launch_cl<VEC, float>(tv, kp, data, ld, nchan, ov, st); break;
-    case 2: launch_cl<VEC, _Float16>(tv, kp, data, ld, nchan, ov, st); break;
-    default: launch_cl<VEC, uint16_t>(tv, kp, data, ld, nchan, ov, st); break;
-  }
-}
-
 hipError_t launch_gather_fp32(const TileView& tv, const KernelParams& kp, const void* data,
                               int dtype, int64_t ld, const float* sdata, int64_t nchan,
                               const OutView& ov, hipStream_t st) {
@@ -411,14 +157,9 @@ hipError_t launch_gather_fp32(const TileView& tv, const KernelParams& kp, const 
     else if (nchan <= 8) CG_TL(8);
     else CG_TL(16);
 #undef CG_TL
-  } else if (nchan <= 64) {
-    launch_cl_dt<1>(tv, kp, data, dtype, ld, nchan, ov, st);
-  } else if (nchan <= 128) {
-    launch_cl_dt<2>(tv, kp, data, dtype, ld, nchan, ov, st);
-  } else {
-    launch_cl_dt<4>(tv, kp, data, dtype, ld, nchan, ov, st);
+    return hipGetLastError();
   }
-  return hipGetLastError();
+  return launch_gather_wide(tv, kp, data, dtype, ld, nchan, ov, st);
 }
 
 // ---------------------------------------------------------------------------

@@ -285,6 +285,26 @@ __device__ __forceinline__ float pair_weight(const KernelParams& kp, double c2, 
   return exp2_neg(d2 * q);
 }
 
+// Target-frame axes for the elliptical kernel: east e = (-sin a, cos a, 0),
+// north n = (-sin d cos a, -sin d sin a, cos d); major axis along
+// cos(pa) n + sin(pa) e, minor axis along cos(pa) e - sin(pa) n.
+__device__ __forceinline__ void target_axes(const KernelParams& kp, double lon, double lat,
+                                            double* a, double* b) {
+  double sa, ca, sd, cd;
+  sincos(lon, &sa, &ca);
+  sincos(lat, &sd, &cd);
+  const double ex = -sa, ey = ca, ez = 0.0;
+  const double nx = -sd * ca, ny = -sd * sa, nz = cd;
+  a[0] = kp.cospa * nx + kp.sinpa * ex;
+  a[1] = kp.cospa * ny + kp.sinpa * ey;
+  a[2] = kp.cospa * nz + kp.sinpa * ez;
+  b[0] = kp.cospa * ex - kp.sinpa * nx;
+  b[1] = kp.cospa * ey - kp.sinpa * ny;
+  b[2] = kp.cospa * ez - kp.sinpa * nz;
+}
+
+__device__ __forceinline__ float qnan_f() { return __int_as_float(0x7fc00000); }
+
 // ---------------------------------------------------------------- launchers
 // All launches are asynchronous on `st`; return hipSuccess or the launch error.
 
@@ -368,6 +388,10 @@ struct OutView {
 hipError_t launch_gather_fp32(const TileView& tv, const KernelParams& kp, const void* data,
                               int dtype, int64_t ld, const float* sdata, int64_t nchan,
                               const OutView& ov, hipStream_t st);
+// the same for more than kSmallC channels (cg_gather_wide.hip)
+hipError_t launch_gather_wide(const TileView& tv, const KernelParams& kp, const void* data,
+                              int dtype, int64_t ld, int64_t nchan, const OutView& ov,
+                              hipStream_t st);
 // zrow: device row of at least nchan zeros of the data type (8 * nchan bytes)
 hipError_t launch_gather_mfma(const TileView& tv, const KernelParams& kp, const void* data,
                               const void* zrow, int dtype, int64_t ld, int64_t nchan, int prec,
