@@ -56,11 +56,7 @@ struct TileView {
 // input row of a sorted sample record
 __device__ __forceinline__ int64_t rec_row(const double4& r) { return __double_as_longlong(r.w); }
 
-// Block -> tile map that keeps consecutive tiles on one XCD: workgroups are
-// dispatched to the 8 XCDs round robin, so block b runs on XCD b % 8; XCD k
-// is given the k-th contiguous run of tiles, walked in order, so that tiles
-// sharing candidate samples are resident together in that XCD's L2.
-constexpr int kNumXcd = 8;
+constexpr int kNumXcd = 8;   // workgroups are dispatched to the XCDs round robin
 
 // Accesses through a pointer that addresses device global memory.  With GL
 // set the pointer is cast to the global address space first: pointers read
@@ -166,18 +162,33 @@ struct RangeWindow {
   }
 };
 
-__device__ __forceinline__ int64_t tile_of_block(int64_t b, int64_t ntiles) {
+// Block -> tile map that keeps neighbouring tiles on one XCD: workgroups are
+// dispatched to the 8 XCDs round robin, so block b runs on XCD b % 8.  The
+// tiles (in visit order) are dealt to the XCDs in runs of `run` consecutive
+// ones, each walked in order, so that tiles sharing candidate samples are
+// resident together in that XCD's L2; what is left after the last full round
+// is split evenly.  A quarter of an XCD's tiles per run keeps a run large
+// against the tiles resident at once on big maps, and spreads the work where
+// the samples cover only a part of the map (a scan of an eighth of a 301 x
+// 257 map, 320 tiles: 0.36 ms with one run per XCD, as all of them fell to
+// one or two XCDs).
+__device__ __forceinline__ int64_t tile_of_block(int64_t b, int64_t ntiles, int64_t npass = 1) {
+  const int64_t run = npass * (1 + ntiles / (npass * kNumXcd * 4));
+  const int64_t round = kNumXcd * run;
   const int64_t k = b % kNumXcd;
   const int64_t j = b / kNumXcd;
-  int64_t start = 0;
-  for (int64_t q = 0; q < k; ++q) start += (ntiles - q + kNumXcd - 1) / kNumXcd;
-  return start + j;
+  const int64_t full = ntiles / round;
+  if (j < full * run) return (j / run) * round + k * run + j % run;
+  const int64_t left = ntiles - full * round;
+  int64_t start = full * round;
+  for (int64_t q = 0; q < k; ++q) start += (left - q + kNumXcd - 1) / kNumXcd;
+  return start + (j - full * run);
 }
 // Same for a 1-D grid of ntiles * npass work items (channel passes of a
 // tile are adjacent, so they run on the same XCD).
 __device__ __forceinline__ void work_of_block(int64_t b, int64_t ntiles, int64_t npass,
                                               int64_t* tile, int64_t* pass) {
-  const int64_t v = tile_of_block(b, ntiles * npass);
+  const int64_t v = tile_of_block(b, ntiles * npass, npass);
   *tile = v / npass;
   *pass = v % npass;
 }
