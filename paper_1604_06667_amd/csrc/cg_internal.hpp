@@ -12,9 +12,7 @@ namespace cg {
 
 constexpr int kTile = 64;              // targets per tile (one wavefront of target slots)
 constexpr int kSmallC = 16;            // up to this many channels the FP32 path stages sorted rows
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 16;         // keys per thread per radix block
-constexpr int kSortTile = kSortThreads * kSortItems;
+constexpr int kSortThreads = 512;
 
 // Kernel constants derived on the host by set_kernel.
 struct KernelParams {
@@ -325,7 +323,7 @@ hipError_t launch_prep(const double* lon, const double* lat, int64_t n, int64_t 
                        int dtype, int64_t ld, int npack, hipStream_t st);
 hipError_t radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp,
                       uint32_t* hist, int64_t n, int bits, bool* result_in_tmp, hipStream_t st);
-size_t radix_hist_elems(int64_t n);   // includes 256 digit totals
+size_t radix_hist_elems(int64_t n);   // histogram and digit totals
 hipError_t launch_ring_offsets(const uint32_t* keys, int64_t n, int64_t nside, uint32_t* ring_off,
                                hipStream_t st);
 // srec: one record per sorted sample (unit vector, input row as int64 bits)

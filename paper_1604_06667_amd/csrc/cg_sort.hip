@@ -99,19 +99,75 @@ hipError_t launch_prep(const double* lon, const double* lat, int64_t n, int64_t 
 }
 
 // ---------------------------------------------------------------------------
-// LSD radix sort of (key, value) uint32 pairs, 8-bit digits.
-// Per pass: block histograms (digit-major), one exclusive scan, and a
-// stable scatter that ranks keys inside each wavefront with ballots.
+// Stable LSD radix sort of (key, value) uint32 pairs.
+//
+// Every pass ranks its pairs inside each wavefront: a wavefront takes 64
+// consecutive pairs per round, ballots find the lanes with the same digit,
+// and a counter per digit, private to the wavefront, adds up the rounds.  The
+// wavefronts' counters are put together once per pass, so a pass needs a few
+// barriers whatever its number of rounds (a prefix over the wavefronts in
+// every round, four barriers each, made the scatter of a 4096-pair block take
+// 14-15 us, and a sort of 20,000 pairs with 30 key bits 95 us instead of 41).
+//
+//   * up to kSmallSort pairs: all passes in one workgroup of 16 wavefronts,
+//     the pairs in registers and exchanged through LDS (3000 pairs with 30
+//     key bits: 80 us with three kernels per pass as it was, 21 us with one;
+//     at 8192 pairs the one workgroup's 35 us meets the passes' 38);
+//   * more: per pass block histograms (digit-major), one exclusive scan per
+//     digit, and a scatter.
+//
+// Digits take up to kDigitBits bits, split evenly over the passes (three
+// passes instead of four: 20,000 pairs 40 us against 44, 47 million 1439
+// against 1492 with digits of at most 8 bits).
 
 constexpr int kMaxJobs = 256;   // the job pass sorts by one 8-bit digit
 
-// Digit of element i: 8 key bits at `shift`, or (JOB) the job holding the
+// Lanes of the wavefront whose digit (nbits wide) equals this lane's, among
+// the lanes with `valid` set.
+template <int NBITS>
+__device__ __forceinline__ uint64_t match_digit(uint32_t d, bool valid) {
+  uint64_t peers = __ballot(valid);
+#pragma unroll
+  for (int b = 0; b < NBITS; ++b) {
+    const bool bit = (d >> b) & 1u;
+    const uint64_t m = __ballot(bit);
+    peers &= bit ? m : ~m;
+  }
+  return peers;
+}
+
+// Rank of this lane's pair among the wavefront's pairs with its digit so far
+// (stable: rounds, then lanes), with the wavefront's counters in cnt[].
+template <int NBITS, typename C>
+__device__ __forceinline__ uint32_t rank_round(C* cnt, uint32_t d, bool valid, int lane) {
+  const uint64_t peers = match_digit<NBITS>(d, valid);
+  const uint64_t below = peers & ((1ull << lane) - 1ull);
+  uint32_t base = 0;
+  if (valid) base = cnt[d];
+  // (LDS accesses of one wavefront are performed in order)
+  __asm__ volatile("" ::: "memory");
+  if (valid && below == 0) cnt[d] = (C)(base + (uint32_t)__popcll(peers));
+  __asm__ volatile("" ::: "memory");
+  return base + (uint32_t)__popcll(below);
+}
+
+// inclusive sum over the wavefront's lanes
+__device__ __forceinline__ uint32_t wave_incl(uint32_t v, int lane) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t y = (uint32_t)__shfl_up((int)v, o, 64);
+    if (lane >= o) v += y;
+  }
+  return v;
+}
+
+// Digit of element i: NBITS key bits at `shift`, or (JOB) the job holding the
 // value, i.e. its position in the concatenated order (job offsets in LDS).
-template <bool JOB>
+template <bool JOB, int NBITS>
 __device__ __forceinline__ uint32_t sort_digit(uint32_t key, uint32_t val, int shift,
                                                const int64_t* s_off, int njobs) {
   if constexpr (JOB) return (uint32_t)job_of(s_off, njobs, (int64_t)val);
-  else return (key >> shift) & 255u;
+  else return (key >> shift) & ((1u << NBITS) - 1u);
 }
 
 template <bool JOB>
@@ -122,33 +178,117 @@ __device__ __forceinline__ void stage_job_offsets(int64_t* s_off, const int64_t*
   }
 }
 
-template <bool JOB>
+// All passes of a small sort in one workgroup.  Round r of wavefront w holds
+// the pairs (w nr + r) 64 + lane.
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallRounds = 8;
+constexpr int64_t kSmallSort = kSmallThreads * kSmallRounds;
+constexpr int kDigitBits = 10;
+
+template <int NBITS>
+__global__ void __launch_bounds__(kSmallThreads) k_sort_small(
+    const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, int n, int npass,
+    uint32_t* __restrict__ kout, uint32_t* __restrict__ vout) {
+  constexpr int NW = kSmallThreads / 64;
+  constexpr int BINS = 1 << NBITS;
+  static_assert(BINS <= kSmallThreads, "one digit per thread");
+  __shared__ uint16_t s_cnt[NW][BINS];   // counts, then first position of each wavefront's digit run
+  __shared__ uint32_t s_k[kSmallSort], s_v[kSmallSort];
+  __shared__ uint32_t s_w[NW];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int nr = (n + kSmallThreads - 1) / kSmallThreads;   // rounds of each wavefront
+  const int first = w * nr * 64 + lane;
+  uint32_t key[kSmallRounds], val[kSmallRounds], rank[kSmallRounds];
+#pragma unroll
+  for (int r = 0; r < kSmallRounds; ++r) {
+    const int i = first + 64 * r;
+    const bool ok = r < nr && i < n;
+    key[r] = ok ? kin[i] : 0u;
+    val[r] = ok ? vin[i] : 0u;
+  }
+  for (int p = 0; p < npass; ++p) {
+    const int shift = p * NBITS;
+    for (int q = t; q < NW * BINS / 2; q += kSmallThreads) reinterpret_cast<uint32_t*>(&s_cnt[0][0])[q] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; ++r)
+      if (r < nr)
+        rank[r] = rank_round<NBITS>(s_cnt[w], (key[r] >> shift) & (BINS - 1), first + 64 * r < n, lane);
+    __syncthreads();
+    // digit t: its counts over the wavefronts, then the digits' prefix
+    uint32_t tot = 0;
+    if (t < BINS) {
+#pragma unroll
+      for (int q = 0; q < NW; ++q) {
+        const uint32_t c = s_cnt[q][t];
+        s_cnt[q][t] = (uint16_t)tot;
+        tot += c;
+      }
+    }
+    const uint32_t incl = wave_incl(tot, lane);
+    if (lane == 63) s_w[w] = incl;
+    __syncthreads();
+    uint32_t base = incl - tot;
+    for (int q = 0; q < w; ++q) base += s_w[q];
+    if (t < BINS) {
+#pragma unroll
+      for (int q = 0; q < NW; ++q) s_cnt[q][t] = (uint16_t)(s_cnt[q][t] + base);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSmallRounds; ++r)
+      if (r < nr && first + 64 * r < n) {
+        const uint32_t pos = rank[r] + s_cnt[w][(key[r] >> shift) & (BINS - 1)];
+        s_k[pos] = key[r];
+        s_v[pos] = val[r];
+      }
+    __syncthreads();
+    if (p + 1 < npass) {
+#pragma unroll
+      for (int r = 0; r < kSmallRounds; ++r) {
+        const int i = first + 64 * r;
+        if (r < nr && i < n) {
+          key[r] = s_k[i];
+          val[r] = s_v[i];
+        }
+      }
+      // (the next pass writes s_k and s_v after three more barriers)
+    }
+  }
+  for (int i = t; i < n; i += kSmallThreads) {
+    kout[i] = s_k[i];
+    vout[i] = s_v[i];
+  }
+}
+
+template <bool JOB, int NBITS, int ITEMS>
 __global__ void __launch_bounds__(kSortThreads) k_hist(const uint32_t* __restrict__ keys,
                                                        const uint32_t* __restrict__ vals, int64_t n,
                                                        int shift, uint32_t* __restrict__ hist,
                                                        int64_t nblocks, const int64_t* joff,
                                                        int njobs) {
-  __shared__ uint32_t h[256];
+  constexpr int BINS = 1 << NBITS;
+  __shared__ uint32_t h[BINS];
   __shared__ int64_t s_off[JOB ? kMaxJobs + 1 : 1];
   const int t = threadIdx.x;
-  h[t] = 0;
+  for (int q = t; q < BINS; q += kSortThreads) h[q] = 0;
   stage_job_offsets<JOB>(s_off, joff, njobs);
   __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
+  const int64_t base = (int64_t)blockIdx.x * (kSortThreads * ITEMS);
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
+  for (int r = 0; r < ITEMS; ++r) {
     const int64_t i = base + (int64_t)r * kSortThreads + t;
     if (i < n) {
-      const uint32_t d = sort_digit<JOB>(JOB ? 0u : keys[i], JOB ? vals[i] : 0u, shift, s_off, njobs);
+      const uint32_t d = sort_digit<JOB, NBITS>(JOB ? 0u : keys[i], JOB ? vals[i] : 0u, shift, s_off, njobs);
       atomicAdd(&h[d], 1u);
     }
   }
   __syncthreads();
-  hist[(int64_t)t * nblocks + blockIdx.x] = h[t];
+  for (int q = t; q < BINS; q += kSortThreads) hist[(int64_t)q * nblocks + blockIdx.x] = h[q];
 }
 
 // Exclusive scan of each digit's per-block counts (one workgroup per digit,
-// coalesced), leaving the digit totals in totals[256].  Each pass over 1024
+// coalesced), leaving the digit totals in totals[].  Each pass over 1024
 // counts gives every thread four consecutive ones; the threads' sums are
 // scanned by shuffles within each wavefront and the four wavefront sums
 // are combined through LDS, one barrier per pass.
@@ -165,12 +305,7 @@ __global__ void __launch_bounds__(256) k_digit_scan(uint32_t* __restrict__ hist,
 #pragma unroll
     for (int q = 0; q < 4; ++q) v[q] = i0 + q < nblocks ? h[i0 + q] : 0u;
     const uint32_t local = v[0] + v[1] + v[2] + v[3];
-    uint32_t incl = local;   // inclusive scan of the threads' sums in the wavefront
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t y = (uint32_t)__shfl_up((int)incl, o, 64);
-      if (lane >= o) incl += y;
-    }
+    const uint32_t incl = wave_incl(local, lane);   // inclusive scan of the threads' sums
     if (lane == 63) s_w[buf][w] = incl;
     __syncthreads();   // (double-buffered sums: the next pass writes the other half)
     uint32_t wbase = 0;
@@ -186,145 +321,153 @@ __global__ void __launch_bounds__(256) k_digit_scan(uint32_t* __restrict__ hist,
   if (t == 0) totals[blockIdx.x] = carry;
 }
 
-// Scatter of one block of kSortTile pairs.  The pairs are first ranked
-// stably by digit (ballots inside each wavefront, a prefix over wavefronts
-// per round) and placed in LDS in block-sorted order; the block then writes
-// them out in that order, so that each digit's run of the block goes to
-// consecutive global positions (whole segments instead of one scattered
+// Scatter of one block of kSortThreads * ITEMS pairs.  The pairs are ranked
+// stably by digit and placed in LDS in block-sorted order; the block then
+// writes them out in that order, so that each digit's run of the block goes
+// to consecutive global positions (whole segments instead of one scattered
 // 4-byte store per pair).
-template <bool JOB>
+template <bool JOB, int NBITS, int ITEMS>
 __global__ void __launch_bounds__(kSortThreads) k_scatter(
     const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin, int64_t n, int shift,
     const uint32_t* __restrict__ hist, const uint32_t* __restrict__ totals, int64_t nblocks,
     uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, const int64_t* joff, int njobs) {
   constexpr int NW = kSortThreads / 64;
-  __shared__ uint32_t gbase[256];     // global position of the block's first pair of digit d
-  __shared__ uint32_t lrun[256];      // pairs of digit d ranked so far, then local offsets
-  __shared__ uint32_t wcnt[NW][256];
-  __shared__ uint32_t sk[kSortTile], sv[kSortTile];
+  constexpr int BINS = 1 << NBITS;
+  constexpr int PER = (BINS + kSortThreads - 1) / kSortThreads;   // consecutive digits per thread
+  constexpr int TILE = kSortThreads * ITEMS;
+  __shared__ uint16_t s_cnt[NW][BINS];   // counts, then first place in the block of a wavefront's run
+  __shared__ uint32_t s_out[BINS];       // global position of a digit's run less its place in the block
+  __shared__ uint32_t s_w[2][NW];
+  __shared__ uint32_t sk[TILE], sv[TILE];
   __shared__ int64_t s_off[JOB ? kMaxJobs + 1 : 1];
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int64_t blk = (int64_t)blockIdx.x * TILE;
+  const int64_t first = blk + w * (64 * ITEMS) + lane;
+  uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const int64_t i = first + 64 * r;
+    key[r] = i < n ? kin[i] : 0u;
+    val[r] = i < n ? vin[i] : 0u;
+  }
+  for (int q = t; q < NW * BINS / 2; q += kSortThreads) reinterpret_cast<uint32_t*>(&s_cnt[0][0])[q] = 0u;
   stage_job_offsets<JOB>(s_off, joff, njobs);
-  const int lane = t & 63;
-  const int w = t >> 6;
-  {
-    // digit bases: exclusive scan of the 256 digit totals
-    const uint32_t v = totals[t];
-    gbase[t] = v;
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-      const uint32_t u = t >= off ? gbase[t - off] : 0u;
-      __syncthreads();
-      gbase[t] += u;
-      __syncthreads();
-    }
-    const uint32_t excl = gbase[t] - v;
-    __syncthreads();
-    gbase[t] = excl + hist[(int64_t)t * nblocks + blockIdx.x];
-    lrun[t] = 0u;
-  }
-  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  const int64_t blk = (int64_t)blockIdx.x * kSortTile;
-  uint32_t key[kSortItems], val[kSortItems], dig[kSortItems], lpos[kSortItems];
+  // digit totals (the whole sort) of this thread's digits, and this block's offsets
+  uint32_t gt[PER], gb[PER], gsum = 0;
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const int64_t i = blk + (int64_t)r * kSortThreads + t;
-    const bool valid = i < n;
-    key[r] = valid ? kin[i] : 0u;
-    val[r] = valid ? vin[i] : 0u;
-  }
-  // ranking: round r holds the pairs blk + r * kSortThreads + (0 .. kSortThreads - 1)
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const bool valid = blk + (int64_t)r * kSortThreads + t < n;
-    const uint32_t d = valid ? sort_digit<JOB>(key[r], val[r], shift, s_off, njobs) : 0u;
-    dig[r] = d;
-    uint64_t peers = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const bool bit = (d >> b) & 1u;
-      const uint64_t m = __ballot(bit);
-      peers &= bit ? m : ~m;
-    }
-    const uint32_t rank = (uint32_t)__popcll(peers & lt_mask);
-    for (int k = t; k < NW * 256; k += kSortThreads) (&wcnt[0][0])[k] = 0u;
-    __syncthreads();
-    if (valid && rank == 0) wcnt[w][d] = (uint32_t)__popcll(peers);
-    __syncthreads();
-    {
-      uint32_t run = lrun[t];
-#pragma unroll
-      for (int q = 0; q < NW; ++q) {
-        const uint32_t c = wcnt[q][t];
-        wcnt[q][t] = run;
-        run += c;
-      }
-      lrun[t] = run;
-    }
-    __syncthreads();
-    lpos[r] = wcnt[w][d] + rank;
-    __syncthreads();
-  }
-  // local offsets: exclusive scan of the block's digit counts
-  {
-    const uint32_t v = lrun[t];
-    __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-      const uint32_t u = t >= off ? lrun[t - off] : 0u;
-      __syncthreads();
-      lrun[t] += u;
-      __syncthreads();
-    }
-    const uint32_t excl = lrun[t] - v;
-    __syncthreads();
-    lrun[t] = excl;
+  for (int q = 0; q < PER; ++q) {
+    const int d = PER * t + q;
+    gt[q] = d < BINS ? totals[d] : 0u;
+    gb[q] = d < BINS ? hist[(int64_t)d * nblocks + blockIdx.x] : 0u;
+    gsum += gt[q];
   }
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    if (blk + (int64_t)r * kSortThreads + t < n) {
-      const uint32_t p = lrun[dig[r]] + lpos[r];
+  for (int r = 0; r < ITEMS; ++r) {
+    const bool ok = first + 64 * r < n;
+    rank[r] = rank_round<NBITS>(s_cnt[w], sort_digit<JOB, NBITS>(key[r], val[r], shift, s_off, njobs), ok, lane);
+  }
+  __syncthreads();
+  // prefix of the counts over the wavefronts, of the digits in the block and
+  // of the digit totals
+  uint32_t lt[PER], lsum = 0;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int d = PER * t + q;
+    uint32_t run = 0;
+    if (d < BINS) {
+#pragma unroll
+      for (int k = 0; k < NW; ++k) {
+        const uint32_t c = s_cnt[k][d];
+        s_cnt[k][d] = (uint16_t)run;
+        run += c;
+      }
+    }
+    lt[q] = run;
+    lsum += run;
+  }
+  const uint32_t lincl = wave_incl(lsum, lane), gincl = wave_incl(gsum, lane);
+  if (lane == 63) {
+    s_w[0][w] = lincl;
+    s_w[1][w] = gincl;
+  }
+  __syncthreads();
+  uint32_t lrun = lincl - lsum, grun = gincl - gsum;
+  for (int k = 0; k < w; ++k) {
+    lrun += s_w[0][k];
+    grun += s_w[1][k];
+  }
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int d = PER * t + q;
+    if (d < BINS) {
+#pragma unroll
+      for (int k = 0; k < NW; ++k) s_cnt[k][d] = (uint16_t)(s_cnt[k][d] + lrun);
+      s_out[d] = grun + gb[q] - lrun;
+    }
+    lrun += lt[q];
+    grun += gt[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r)
+    if (first + 64 * r < n) {
+      const uint32_t p =
+          s_cnt[w][sort_digit<JOB, NBITS>(key[r], val[r], shift, s_off, njobs)] + rank[r];
       sk[p] = key[r];
       sv[p] = val[r];
     }
-  }
   __syncthreads();
-  const int nb = (int)((n - blk) < (int64_t)kSortTile ? (n - blk) : (int64_t)kSortTile);
-  for (int j = t; j < nb; j += kSortThreads) {
-    const uint32_t k = sk[j], v = sv[j];
-    const uint32_t d = sort_digit<JOB>(k, v, shift, s_off, njobs);
-    const uint32_t pos = gbase[d] + ((uint32_t)j - lrun[d]);
-    kout[pos] = k;
-    vout[pos] = v;
+  const int nb = (int)((n - blk) < (int64_t)TILE ? (n - blk) : (int64_t)TILE);
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const int j = r * kSortThreads + t;
+    if (j < nb) {
+      const uint32_t k = sk[j], v = sv[j];
+      const uint32_t pos = s_out[sort_digit<JOB, NBITS>(k, v, shift, s_off, njobs)] + (uint32_t)j;
+      kout[pos] = k;
+      vout[pos] = v;
+    }
   }
+}
+
+// Pairs per thread of a block: few while that leaves at most 256 blocks (one
+// per CU), as a pass is then a chain of latencies (524288 pairs of 30 bits: 62
+// us with 4 against 82 with 16; a million: 75 with 8, 85 with 16); many beyond,
+// for long runs of a digit in the writes (47.2 million of 26 bits: 1196 us with
+// 16 and 512 threads, 1439 with 256 threads, 3323 with 4).
+static int sort_items(int64_t n) {
+  return n <= 256 * 4 * kSortThreads ? 4 : n <= 256 * 8 * kSortThreads ? 8 : 16;
 }
 
 size_t radix_hist_elems(int64_t n) {
-  const int64_t nb = (n + kSortTile - 1) / kSortTile;
-  return (size_t)(nb < 1 ? 1 : nb) * 256 + 256;
+  const int64_t tile = (int64_t)kSortThreads * sort_items(n);
+  const int64_t nb = (n + tile - 1) / tile;
+  return ((size_t)(nb < 1 ? 1 : nb) + 1) << kDigitBits;
 }
 
-static void sort_pass(bool job, uint32_t*& ki, uint32_t*& vi, uint32_t*& ko, uint32_t*& vo,
-                      uint32_t* hist, int64_t n, int64_t nb, int shift, const int64_t* joff,
-                      int njobs, hipStream_t st) {
-  uint32_t* totals = hist + nb * 256;
-  if (job) {
-    hipLaunchKernelGGL(k_hist<true>, dim3((unsigned)nb), dim3(kSortThreads), 0, st, ki, vi, n,
-                       shift, hist, nb, joff, njobs);
-  } else {
-    hipLaunchKernelGGL(k_hist<false>, dim3((unsigned)nb), dim3(kSortThreads), 0, st, ki, vi, n,
-                       shift, hist, nb, joff, njobs);
-  }
-  hipLaunchKernelGGL(k_digit_scan, dim3(256), dim3(256), 0, st, hist, nb, totals);
-  if (job) {
-    hipLaunchKernelGGL(k_scatter<true>, dim3((unsigned)nb), dim3(kSortThreads), 0, st, ki, vi, n,
-                       shift, hist, totals, nb, ko, vo, joff, njobs);
-  } else {
-    hipLaunchKernelGGL(k_scatter<false>, dim3((unsigned)nb), dim3(kSortThreads), 0, st, ki, vi, n,
-                       shift, hist, totals, nb, ko, vo, joff, njobs);
-  }
-  uint32_t* tk = ki; ki = ko; ko = tk;
-  uint32_t* tv = vi; vi = vo; vo = tv;
+template <bool JOB, int NBITS, int ITEMS>
+static void sort_pass(const uint32_t* ki, const uint32_t* vi, uint32_t* ko, uint32_t* vo,
+                      uint32_t* hist, int64_t n, int shift, const int64_t* joff, int njobs,
+                      hipStream_t st) {
+  const int64_t tile = (int64_t)kSortThreads * ITEMS;
+  const int64_t nb = (n + tile - 1) / tile;
+  uint32_t* totals = hist + (nb << NBITS);
+  const dim3 g((unsigned)nb), b(kSortThreads);
+  hipLaunchKernelGGL((k_hist<JOB, NBITS, ITEMS>), g, b, 0, st, ki, vi, n, shift, hist, nb, joff, njobs);
+  hipLaunchKernelGGL(k_digit_scan, dim3(1u << NBITS), dim3(256), 0, st, hist, nb, totals);
+  hipLaunchKernelGGL((k_scatter<JOB, NBITS, ITEMS>), g, b, 0, st, ki, vi, n, shift, hist, totals, nb, ko,
+                     vo, joff, njobs);
+}
+
+template <bool JOB, int NBITS>
+static void sort_pass_items(const uint32_t* ki, const uint32_t* vi, uint32_t* ko, uint32_t* vo,
+                            uint32_t* hist, int64_t n, int shift, const int64_t* joff, int njobs,
+                            hipStream_t st) {
+  const int items = sort_items(n);
+  if (items == 4) sort_pass<JOB, NBITS, 4>(ki, vi, ko, vo, hist, n, shift, joff, njobs, st);
+  else if (items == 8) sort_pass<JOB, NBITS, 8>(ki, vi, ko, vo, hist, n, shift, joff, njobs, st);
+  else sort_pass<JOB, NBITS, 16>(ki, vi, ko, vo, hist, n, shift, joff, njobs, st);
 }
 
 hipError_t radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp,
@@ -339,16 +482,31 @@ hipError_t radix_sort_jobs(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, u
   *result_in_tmp = false;
   if (n <= 1) return hipSuccess;
   if (njobs > kMaxJobs) return hipErrorInvalidValue;
-  const int64_t nb = (n + kSortTile - 1) / kSortTile;
   uint32_t *ki = keys, *vi = vals, *ko = keys_tmp, *vo = vals_tmp;
   bool in_tmp = false;
-  for (int shift = 0; shift < bits; shift += 8) {
-    sort_pass(false, ki, vi, ko, vo, hist, n, nb, shift, noff, njobs, st);
+  auto flip = [&]() {
+    uint32_t* tk = ki; ki = ko; ko = tk;
+    uint32_t* tv = vi; vi = vo; vo = tv;
     in_tmp = !in_tmp;
+  };
+  const int npass = bits > 0 ? (bits + kDigitBits - 1) / kDigitBits : 0;
+  const int db = npass > 0 ? (bits + npass - 1) / npass : 8;   // bits per digit
+  if (npass > 0 && n <= kSmallSort) {
+    if (db <= 8) hipLaunchKernelGGL(k_sort_small<8>, dim3(1), dim3(kSmallThreads), 0, st, ki, vi, (int)n, npass, ko, vo);
+    else if (db == 9) hipLaunchKernelGGL(k_sort_small<9>, dim3(1), dim3(kSmallThreads), 0, st, ki, vi, (int)n, npass, ko, vo);
+    else hipLaunchKernelGGL(k_sort_small<10>, dim3(1), dim3(kSmallThreads), 0, st, ki, vi, (int)n, npass, ko, vo);
+    flip();
+  } else {
+    for (int p = 0; p < npass; ++p) {
+      if (db <= 8) sort_pass_items<false, 8>(ki, vi, ko, vo, hist, n, 8 * p, noff, njobs, st);
+      else if (db == 9) sort_pass_items<false, 9>(ki, vi, ko, vo, hist, n, 9 * p, noff, njobs, st);
+      else sort_pass_items<false, 10>(ki, vi, ko, vo, hist, n, 10 * p, noff, njobs, st);
+      flip();
+    }
   }
   if (njobs > 1) {
-    sort_pass(true, ki, vi, ko, vo, hist, n, nb, 0, noff, njobs, st);
-    in_tmp = !in_tmp;
+    sort_pass_items<true, 8>(ki, vi, ko, vo, hist, n, 0, noff, njobs, st);
+    flip();
   }
   *result_in_tmp = in_tmp;
   return hipGetLastError();
