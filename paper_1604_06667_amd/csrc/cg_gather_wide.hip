@@ -64,14 +64,7 @@ __device__ __forceinline__ void load_raw4(const T* __restrict__ p, int nvalid, b
   for (int i = 0; i < 4; ++i) o[i] = i < nvalid ? p[i] : (T)0;
 }
 
-// LDS accesses of one wavefront are performed in order: only the compiler has
-// to keep them so
-__device__ __forceinline__ void wave_lds_order() {
-  __builtin_amdgcn_wave_barrier();
-  __asm__ volatile("" ::: "memory");
-}
-
-template <int CWV, int KW, int KT, typename T>
+template <int CWV, int KW, int KT, bool SHORT, typename T>
 __global__ void __launch_bounds__(64 * CWV * KW, 2) k_gather_wide(
     TileView tv, KernelParams kp, const T* __restrict__ data, int64_t ld, int64_t nchan,
     int vec_ok_in, OutView ov) {
@@ -257,12 +250,8 @@ __global__ void __launch_bounds__(64 * CWV * KW, 2) k_gather_wide(
         const double dx = rc[k][0] - tx, dy = rc[k][1] - ty, dz = rc[k][2] - tz;
         const double c2 = dx * dx + dy * dy + dz * dz;
         float w = 0.0f;
-        if (c2 <= kp.cs2 && 4 * s + lk < hits) {
-          if (KT == 0)
-            w = exp2_neg(chord2_to_d2_for(kp, c2) * kp.k1);
-          else
-            w = pair_weight<KT == 3>(kp, c2, dx, dy, dz, tt[3], tt[4], tt[5], tt[6], tt[7], tt[8]);
-        }
+        if (c2 <= kp.cs2 && 4 * s + lk < hits)
+          w = pair_weight<KT, SHORT>(kp, c2, dx, dy, dz, tt[3], tt[4], tt[5], tt[6], tt[7], tt[8]);
         s_w[buf][kw][g][s][lane] = w;
         wl[q] += (double)w;
       }
@@ -447,12 +436,15 @@ void launch_kt(const TileView& tv, const KernelParams& kp, const void* data, int
   // vector loads need every row start aligned to four elements
   const int vec_ok = (ld % 4 == 0) && ((uintptr_t)data % (4 * sizeof(T)) == 0) ? 1 : 0;
   const T* d = (const T*)data;
-  if (kp.type == 0)
-    hipLaunchKernelGGL((k_gather_wide<CWV, KW, 0, T>), g, b, 0, st, tv, kp, d, ld, nchan, vec_ok, ov);
-  else if (kp.type == 1)
-    hipLaunchKernelGGL((k_gather_wide<CWV, KW, 1, T>), g, b, 0, st, tv, kp, d, ld, nchan, vec_ok, ov);
-  else
-    hipLaunchKernelGGL((k_gather_wide<CWV, KW, 3, T>), g, b, 0, st, tv, kp, d, ld, nchan, vec_ok, ov);
+#define CG_WIDE(KT, SH) \
+  hipLaunchKernelGGL((k_gather_wide<CWV, KW, KT, SH, T>), g, b, 0, st, tv, kp, d, ld, nchan, vec_ok, ov)
+  const bool sh = short_support(kp);
+  if (kp.type >= 2) CG_WIDE(3, false);
+  else if (kp.type == 0 && sh) CG_WIDE(0, true);
+  else if (kp.type == 0) CG_WIDE(0, false);
+  else if (sh) CG_WIDE(1, true);
+  else CG_WIDE(1, false);
+#undef CG_WIDE
 }
 
 template <typename T>

@@ -230,13 +230,6 @@ __device__ __forceinline__ double chord2_to_d2(double c2) {
   return chord2_to_d2_exact(c2);
 }
 
-// The same for the pairs of one launch: supports up to ~0.57 deg (c^2 <=
-// 1e-4, uniform over the launch) keep d^2 = c^2 (1 + c^2/12), whose next term
-// is below 1.1e-10 relative, in two FP64 operations.
-__device__ __forceinline__ double chord2_to_d2_for(const KernelParams& kp, double c2) {
-  return kp.cs2 <= 1e-4 ? fma(c2 * c2, 1.0 / 12.0, c2) : chord2_to_d2(c2);
-}
-
 // 2^(-x) for x >= 0 given in FP64, evaluated as 2^-frac (FP32) * 2^-int so
 // that rounding x to FP32 does not cost accuracy at large x.
 __device__ __forceinline__ float exp2_neg(double x) {
@@ -270,18 +263,24 @@ __device__ __forceinline__ double radial_weight(const KernelParams& kp, double d
   return kp.tab[i] + f * (kp.tab[i + 1] - kp.tab[i]);
 }
 
-// RADIAL: the kernel is one of the radial shapes (types 2, 3); otherwise a
-// Gaussian (types 0, 1).  Separate instantiations keep the Gaussian loops
-// free of the radial code's registers.
-template <bool RADIAL>
+// The kernel type and the distance form of a launch, fixed at compile time so
+// that the loops over pairs carry no branch for them: KT 0 circular Gaussian,
+// 1 elliptical, 3 one of the radial shapes (chosen at run time); SHORT: a
+// support of at most ~0.57 deg (short_support).
+__host__ __device__ __forceinline__ bool short_support(const KernelParams& kp) {
+  return kp.cs2 <= 1e-4;
+}
+template <int KT, bool SHORT>
 __device__ __forceinline__ float pair_weight(const KernelParams& kp, double c2, double dx, double dy,
                                              double dz, double ax, double ay, double az, double bx,
                                              double by, double bz) {
-  const double d2 = chord2_to_d2_for(kp, c2);
-  if constexpr (RADIAL) return (float)radial_weight(kp, d2);
-  if (kp.type == 0) return exp2_neg(d2 * kp.k1);
+  // short supports keep d^2 = c^2 (1 + c^2/12), whose next term is below
+  // 1.1e-10 relative, in two FP64 operations
+  const double d2 = SHORT ? fma(c2 * c2, 1.0 / 12.0, c2) : chord2_to_d2(c2);
+  if constexpr (KT == 3) return (float)radial_weight(kp, d2);
+  if constexpr (KT == 0) return exp2_neg(d2 * kp.k1);
   const double u = dx * ax + dy * ay + dz * az;
-  if (kp.cs2 <= 1e-4) {
+  if constexpr (SHORT) {
     // u^2 + v^2 is the chord's tangential part c^2 (1 - c^2/4) exactly, so
     // the exponent is d^2 kmin + (kmaj - kmin) u^2 d^2 / (c^2 (1 - c^2/4)),
     // and for these supports d^2 / (c^2 (1 - c^2/4)) = 1 + c^2/3 to 1e-9
@@ -313,6 +312,13 @@ __device__ __forceinline__ void target_axes(const KernelParams& kp, double lon, 
 }
 
 __device__ __forceinline__ float qnan_f() { return __int_as_float(0x7fc00000); }
+
+// LDS accesses of one wavefront are performed in order: only the compiler has
+// to keep them so
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_wave_barrier();
+  __asm__ volatile("" ::: "memory");
+}
 
 // ---------------------------------------------------------------- launchers
 // All launches are asynchronous on `st`; return hipSuccess or the launch error.
