@@ -37,7 +37,12 @@ struct cg_batch {
   bool items_valid = false;
   std::vector<int64_t> items_for_n;          // sample counts the queue was ordered for
   // tuned launch shape (cg::launch_batch_mfma), item width, workgroups per CU
-  int shape = 1, split = 0, bpc = 0;
+  // (untuned: 256 channels per item, four wavefronts of two channel blocks,
+  // the tuner's choice on all of four batches of 6 to 16 jobs; the largest
+  // takes 3.0 ms so, 3.4 with eight wavefronts of one block and 3.5 of two)
+  int shape = 3, split = 0, bpc = 0;
+  // kernel form of the uploaded job table, and of the captured graph
+  int form = cg::BATCH_ANY, graph_form = cg::BATCH_ANY;
   // graph
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
@@ -176,6 +181,17 @@ cg_status build_items(cg_batch* b, const cg_batch_job* in, hipStream_t st) {
   return CG_OK;
 }
 
+// What the kernels of all jobs have in common (the forms are ordered: each
+// also serves the batches of the ones before it).
+int form_of(const cg_batch* b) {
+  int form = cg::BATCH_SHORT_CIRCULAR;
+  for (const cg_gridder* g : b->jobs) {
+    if (!cg::short_support(g->kp)) return cg::BATCH_ANY;
+    if (g->kp.type != 0) form = cg::BATCH_SHORT;
+  }
+  return form;
+}
+
 // Job table and offsets for the inputs `in`; uploads them on `st`.
 cg_status upload_tables(cg_batch* b, const cg_batch_job* in, hipStream_t st) {
   const int njobs = (int)b->jobs.size();
@@ -224,6 +240,7 @@ cg_status upload_tables(cg_batch* b, const cg_batch_job* in, hipStream_t st) {
     q.kp = g->kp;
     q.rho = g->support_rad + 1e-9;
   }
+  b->form = form_of(b);
   // staging buffers are reused: the previous upload must be complete
   CG_HIP(hipStreamSynchronize(st), "sync tables");
   memcpy(b->pin_jobs, b->hjobs.data(), sizeof(cg::BatchJob) * (size_t)njobs);
@@ -298,7 +315,7 @@ cg_status contract_part(cg_batch* b, hipStream_t st, bool events) {
   br.ncand = b->ncand.as<uint64_t>();
   br.srec = reinterpret_cast<const double4*>(b->sx.as<double>());
   CG_HIP(cg::launch_batch_mfma(dj, b->items.as<cg::BatchItem>(), b->queues, b->counter.as<int>(),
-                               br, b->zrow.p, b->dtype, b->prec, b->shape, b->bpc, st),
+                               br, b->zrow.p, b->dtype, b->prec, b->shape, b->form, b->bpc, st),
          "batch contraction");
   if (pe) CG_HIP(hipEventRecord(pe->second, st), "event record");
   return CG_OK;
@@ -388,6 +405,7 @@ cg_status cg_batch_create(cg_batch** out, cg_gridder* const* jobs, int32_t njobs
     b->snap_ranges.push_back(g->total_ranges);
     maxside = std::max(maxside, g->nside);
   }
+  b->form = form_of(b);
   b->ntiles = b->toff[(size_t)njobs];
   b->nro = b->rooff[(size_t)njobs];
   b->nranges_tot = b->rbase[(size_t)njobs];
@@ -442,7 +460,7 @@ cg_status cg_batch_tune(cg_batch* b, const cg_batch_job* in, int32_t reps, void*
   float best = 1e30f;
   int bb = b->shape, bs = b->split, bc = b->bpc;
   for (int shape = 0; shape < cg::kBatchShapes; ++shape) {
-    const int occ = cg::batch_max_blocks_per_cu(b->dtype, b->prec, shape);
+    const int occ = cg::batch_max_blocks_per_cu(b->dtype, b->prec, shape, b->form);
     std::vector<int> shapes = {occ};
     if (occ > 1) shapes.push_back(1);
     for (int split : {0, 1}) {
@@ -518,6 +536,7 @@ cg_status cg_batch_capture(cg_batch* b, const cg_batch_job* in, void* stream) {
   }
   b->graph = graph;
   b->exec = exec;
+  b->graph_form = b->form;
   return CG_OK;
 }
 
@@ -537,7 +556,14 @@ cg_status cg_batch_replay(cg_batch* b, void* stream) {
   cg_status s = batch_event(b, &pe);
   if (s != CG_OK) return s;
   if (pe) CG_HIP(hipEventRecord(pe->first, st), "event record");
-  CG_HIP(hipGraphLaunch(b->exec, st), "graph launch");
+  if (b->form > b->graph_form) {
+    // a pass since the capture has uploaded kernels that the graph's
+    // contraction does not cover: the same work, launched one by one
+    if ((s = lookup_part(b, st)) != CG_OK) return s;
+    if ((s = contract_part(b, st, false)) != CG_OK) return s;
+  } else {
+    CG_HIP(hipGraphLaunch(b->exec, st), "graph launch");
+  }
   if (pe) CG_HIP(hipEventRecord(pe->second, st), "event record");
   return CG_OK;
 }
@@ -578,7 +604,7 @@ cg_status cg_batch_query(const cg_batch* b, int32_t what, int64_t* value) {
     }
     case 5: *value = cg::batch_shape_rows(b->shape); break;
     case 6: *value = b->split; break;
-    case 7: *value = b->bpc > 0 ? b->bpc : cg::batch_max_blocks_per_cu(b->dtype, b->prec, b->shape); break;
+    case 7: *value = b->bpc > 0 ? b->bpc : cg::batch_max_blocks_per_cu(b->dtype, b->prec, b->shape, b->form); break;
     case 9: *value = b->shape; break;
     case 8: *value = b->exec ? 1 : 0; break;
     default: return fail(CG_E_INVALID, "unknown query %d", what);

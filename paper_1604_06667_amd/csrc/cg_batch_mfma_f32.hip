@@ -1,0 +1,11 @@
+// Persistent batch contraction kernels of float32 data.
+#include "cg_batch_mfma_launch.hpp"
+
+namespace cg {
+
+template hipError_t launch_batch_mfma_t<float>(const BatchJob*, const BatchItem*, const BatchQueues&, int*,
+                                             const BatchRanges&, const void*, int, int, int, int,
+                                             hipStream_t);
+template int batch_max_blocks_per_cu_t<float>(int, int, int);
+
+}  // namespace cg

@@ -495,10 +495,16 @@ struct BatchQueues {
 // batch_shape_rows(shape) channels per item); counter holds kNumXcd ints,
 // zero at launch.
 constexpr int kBatchShapes = 4;
+// Kernel form of a batch: what all of its jobs have in common.
+enum BatchForm {
+  BATCH_SHORT_CIRCULAR = 0,   // circular kernels, short supports (short_support)
+  BATCH_SHORT = 1,            // either kernel type, short supports
+  BATCH_ANY = 2
+};
 hipError_t launch_batch_mfma(const BatchJob* jobs, const BatchItem* items, const BatchQueues& q,
                              int* counter, const BatchRanges& br, const void* zrow, int dtype,
-                             int prec, int shape, int blocks_per_cu, hipStream_t st);
-int batch_max_blocks_per_cu(int dtype, int prec, int shape);
+                             int prec, int shape, int form, int blocks_per_cu, hipStream_t st);
+int batch_max_blocks_per_cu(int dtype, int prec, int shape, int form);
 int batch_shape_rows(int shape);
 hipError_t launch_stats(const TileView& tv, const KernelParams& kp, const int32_t* slot_target,
                         int32_t* counts, uint64_t* hashes, hipStream_t st);

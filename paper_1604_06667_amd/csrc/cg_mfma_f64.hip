@@ -1,0 +1,9 @@
+// Matrix-core contraction kernels of float64 data.
+#include "cg_mfma_launch.hpp"
+
+namespace cg {
+
+template hipError_t launch_gather_mfma_t<double>(const TileView&, const KernelParams&, const void*, const void*,
+                                              int64_t, int64_t, int, const OutView&, hipStream_t);
+
+}  // namespace cg

@@ -113,7 +113,8 @@ __device__ __forceinline__ void load4(const T* __restrict__ p, int nvalid, bool 
 constexpr int kListCands = 4096;    // candidates of a tile listed in LDS
 constexpr int kListRanges = 512;    // ranges of a tile listed in LDS
 
-template <int NW, int BPW, int KT, int MODE, bool FULL, typename T, int KS = 1, bool GL = false>
+template <int NW, int BPW, int KT, bool SHORT, int MODE, bool FULL, typename T, int KS = 1,
+          bool GL = false>
 __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams kp,
                                           const T* __restrict__ data, const T* __restrict__ zrow,
                                           int64_t ld, int64_t nchan, const OutView ov,
@@ -124,7 +125,7 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
   constexpr bool BF16IN = std::is_same<T, uint16_t>::value;
   constexpr int NS = SPLIT ? 2 : 1;              // hi (+ lo) parts
   constexpr int MK = 16 * KS;                    // candidate samples per chunk
-  static_assert(MK <= NW * 64, "one candidate record per thread");
+  static_assert(MK <= NW * 64 && MK % NW == 0, "one candidate record per thread");
   constexpr int KP = MK + 8;                     // padded LDS row of the weight block
   constexpr int CP = NW * BPW * 32;              // channels per pass
   using opv_t = typename std::conditional<F16, f16x8_t, bf16x8_t>::type;
@@ -146,7 +147,10 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
   const int64_t cbase = c0 + wv * BPW * 32 + cl;   // this lane's channel in block 0
   // KT: 0 gauss1d, 1 gauss2d, 2 either, chosen at run time (batched jobs of
   // both types), 3 a radial kernel of arbitrary shape (tapered sinc or
-  // tabulated profile, chosen at run time)
+  // tabulated profile, chosen at run time).  SHORT: the support of the launch
+  // (of every job) is at most ~0.57 deg, so that the weights carry no branch
+  // and no call for longer chords (whose call convention alone held the
+  // kernel to 120 registers)
   const bool ell = KT == 1 || (KT == 2 && kp.type == 1);
   bool bvalid[BPW];    // this lane's channel of block b exists
   bool bany[BPW];      // block b has any channel (uniform over the wavefront)
@@ -178,10 +182,15 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
       for (int q = 0; q < 3; ++q) s_ax[t][q] = a[q];
     }
   }
-  // this thread's target in the weight block and its candidates kg, kg + NW, ...
+  // this thread's target in the weight block and its candidates WPT kg .. WPT kg + WPT - 1
+  constexpr int WPT = MK / NW;
+  static_assert(WPT % 2 == 0, "weights in pairs");
   const int nw = t & 63;
   const int kg = t >> 6;
   double wsum = 0.0, wsum_r = 0.0;
+  // where the accumulators leave room, the target stays in registers
+  constexpr bool REGT = BPW <= 2;
+  double wtx = 0.0, wty = 0.0, wtz = 0.0, wax = 0.0, way = 0.0, waz = 0.0;
 
   f32x16_t acc[BPW][2];
 #pragma unroll
@@ -265,7 +274,7 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
     s_c[buf][t][2] = rz;
     s_row[buf][t] = rok ? rrow * ld : zoff;
   };
-  // weight of candidate k of the chunk in record buffer rb -> weight buffer wb
+  // weight of candidate k of the chunk in record buffer rb
   // Kernel value of a pair.  The support test is FP64 on the chord.  The
   // value is rounded to 16-bit operand parts, but the weight map sums it
   // unrounded, so it is held to about 2e-7 relative: the base-2 exponent's
@@ -282,21 +291,21 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
   // which needs only u.  With d^2 = c^2 (1 + s), s = c^2/12 + c^4/90 + ...,
   // and rq = 1 + (s + c^2/4) / (1 - c^2/4), the exponent is the leading term
   // plus kmin c^2 s + (kmaj - kmin) u^2 (rq - 1).  Supports below ~0.57 deg
-  // (c^2 <= 1e-4, uniform over the launch) keep s = c^2/12 and rq - 1 =
-  // c^2/3, whose next terms are below 1e-8 relative.
+  // (SHORT: c^2 <= 1e-4) keep s = c^2/12 and rq - 1 = c^2/3, whose next
+  // terms are below 1e-8 relative.
   const float k1f = (float)kp.k1, kminf = (float)kp.kmin, kdf = (float)(kp.kmaj - kp.kmin);
   const float ksf = (float)kp.ks, tinvf = (float)kp.tinv;
   const double kdd = kp.kmaj - kp.kmin;
-  const bool short_support = kp.cs2 <= 1e-4;
-  auto weight = [&](int rb, int wb, int k) {
-    const double dx = s_c[rb][k][0] - s_tg[nw][0];
-    const double dy = s_c[rb][k][1] - s_tg[nw][1];
-    const double dz = s_c[rb][k][2] - s_tg[nw][2];
+  auto weight = [&](int rb, int k, auto elliptical) -> float {
+    constexpr bool ELL = decltype(elliptical)::value;
+    const double dx = s_c[rb][k][0] - (REGT ? wtx : s_tg[nw][0]);
+    const double dy = s_c[rb][k][1] - (REGT ? wty : s_tg[nw][1]);
+    const double dz = s_c[rb][k][2] - (REGT ? wtz : s_tg[nw][2]);
     const double c2 = dx * dx + dy * dy + dz * dz;
     const float c = (float)c2;
     // s = d^2 / c^2 - 1 (series, or exact for chords beyond ~20 deg)
     auto series = [&]() -> float {
-      if (short_support) return c * (1.0f / 12.0f);
+      if constexpr (SHORT) return c * (1.0f / 12.0f);
       if (c2 > 0.1225) return (float)(chord2_to_d2_exact(c2) / c2 - 1.0);
       return c * (1.0f / 12.0f + c * (1.0f / 90.0f + c * (1.0f / 560.0f +
              c * (1.0f / 3150.0f + c * (1.0f / 16632.0f)))));
@@ -328,14 +337,16 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
       const float sr = series();
       double xl = c2 * kp.k1;        // leading term of the exponent
       float corr = (float)xl * sr;   // the rest
-      if constexpr (KT == 1 || KT == 2) {
-        if (ell) {
-          const double u = dx * s_ax[nw][0] + dy * s_ax[nw][1] + dz * s_ax[nw][2];
-          const double u2 = u * u;
+      if constexpr (ELL) {
+        const double u = dx * (REGT ? wax : s_ax[nw][0]) + dy * (REGT ? way : s_ax[nw][1]) +
+                         dz * (REGT ? waz : s_ax[nw][2]);
+        const double u2 = u * u;
+        xl = fma(kdd, u2, c2 * kp.kmin);
+        if constexpr (SHORT) {   // s = c / 12, rq - 1 = c / 3
+          corr = c * fmaf(kdf * (1.0f / 3.0f), (float)u2, kminf * (1.0f / 12.0f) * c);
+        } else {
           const float den = 1.0f - 0.25f * c;   // zero only for an antipodal sample (u = 0)
-          const float rq1 = short_support ? c * (1.0f / 3.0f)
-                            : den > 0.0f ? (sr + 0.25f * c) * __builtin_amdgcn_rcpf(den) : 0.0f;
-          xl = fma(kdd, u2, c2 * kp.kmin);
+          const float rq1 = den > 0.0f ? (sr + 0.25f * c) * __builtin_amdgcn_rcpf(den) : 0.0f;
           corr = kminf * c * sr + kdf * (float)u2 * rq1;
         }
       }
@@ -347,26 +358,41 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
       const float v = ldexpf(__builtin_amdgcn_exp2f(-((float)(xl - fl) + corr)), (int)(-fl));
       w = c2 <= kp.cs2 ? v : 0.0f;
     }
-    const uint16_t whi = to_bits<F16>(w);
-    float wr = from_bits<F16>(whi);
-    s_wt[wb][0][nw * KP + k] = whi;
+    return w;
+  };
+  // The kernel values of two neighbouring candidates k, k + 1 of a chunk (one
+  // packed conversion and one LDS store per part), summed for the weight map
+  // unrounded and for the normaliser as they enter the products.
+  auto put_weights = [&](int wb, int k, float w0, float w1) {
+    const uint32_t hi = cvt_pk<F16>(w0, w1);
+    float r0 = unpk_lo<F16>(hi), r1 = unpk_hi<F16>(hi);
+    *reinterpret_cast<uint32_t*>(&s_wt[wb][0][nw * KP + k]) = hi;
     if constexpr (SPLIT) {
-      const uint16_t wlo = to_bits<F16>(w - wr);
-      s_wt[wb][NS - 1][nw * KP + k] = wlo;
-      wr += from_bits<F16>(wlo);
+      const uint32_t lo = cvt_pk<F16>(w0 - r0, w1 - r1);
+      *reinterpret_cast<uint32_t*>(&s_wt[wb][NS - 1][nw * KP + k]) = lo;
+      r0 += unpk_lo<F16>(lo);
+      r1 += unpk_hi<F16>(lo);
     }
-    wsum += (double)w;
-    wsum_r += (double)wr;
+    wsum += (double)w0;
+    wsum += (double)w1;
+    wsum_r += (double)r0;
+    wsum_r += (double)r1;
+  };
+  auto weight_pair = [&](int rb, int wb, int k) {
+    if (KT == 1 || (KT == 2 && ell))
+      put_weights(wb, k, weight(rb, k, std::true_type{}), weight(rb, k + 1, std::true_type{}));
+    else
+      put_weights(wb, k, weight(rb, k, std::false_type{}), weight(rb, k + 1, std::false_type{}));
   };
   // this lane's A-operand values (raw input) of one chunk
-  // 16-bit input of the operand's own type is used bit for bit (two values
-  // packed per register); any other input is converted through FP32.
+  // 16-bit input of the operand's own type is used bit for bit; any other input is converted through FP32.
   constexpr bool DIRECT = (BF16IN && !F16) || (std::is_same<T, _Float16>::value && F16);
-  float raw[BPW][KS][DIRECT ? 1 : 8];
-  uint32_t rawp[BPW][KS][4];
+  using raw_t = typename std::conditional<DIRECT, uint32_t, float>::type;
+  raw_t raw[BPW][KS][8];
   // Lanes whose channel lies past cend read the last valid channel of the
-  // same row instead (and discard it), so that every address stays inside
-  // the caller's row (or the zero row) whatever the channel count.
+  // same row instead, so that every address stays inside the caller's row (or
+  // the zero row) whatever the channel count; their rows of the products are
+  // never written.
   auto load_block = [&](int rb, int b) {
     const int64_t cofs = bvalid[b] ? cbase + 32 * b : cend - 1;
 #pragma unroll
@@ -375,15 +401,12 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
       if constexpr (DIRECT) {
         const uint16_t* d16 = reinterpret_cast<const uint16_t*>(data);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const uint32_t lo = ldg<GL>(d16, rw[2 * q] + cofs), hi = ldg<GL>(d16, rw[2 * q + 1] + cofs);
-          rawp[b][s][q] = bvalid[b] ? __builtin_amdgcn_perm(hi, lo, 0x05040100u) : 0u;
-        }
+        for (int i = 0; i < 8; ++i) raw[b][s][i] = (uint32_t)ldg<GL>(d16, rw[i] + cofs);
       } else {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const T v = ldg<GL>(data, rw[i] + cofs);
-          raw[b][s][i] = bvalid[b] ? in_f32<T>(&v) : 0.0f;
+          raw[b][s][i] = in_f32<T>(&v);
         }
       }
     }
@@ -399,9 +422,15 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
     load_rec(2);
   }
   __syncthreads();
+  if constexpr (REGT) {
+    wtx = s_tg[nw][0]; wty = s_tg[nw][1]; wtz = s_tg[nw][2];
+    if constexpr (KT == 1 || KT == 2) {
+      wax = s_ax[nw][0]; way = s_ax[nw][1]; waz = s_ax[nw][2];
+    }
+  }
   if (nchunks > 0) {
 #pragma unroll
-    for (int k = kg; k < MK; k += NW) weight(0, 0, k);
+    for (int q = 0; q < WPT; q += 2) weight_pair(0, 0, kg * WPT + q);
 #pragma unroll
     for (int b = 0; b < BPW; ++b) load_block(0, b);
   }
@@ -435,9 +464,14 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
         uint32_t hp[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          if constexpr (DIRECT) hp[q] = rawp[b][s][q];
+          if constexpr (DIRECT)   // (packed only here, so that the loads stay in flight until now)
+            hp[q] = __builtin_amdgcn_perm(raw[b][s][2 * q + 1], raw[b][s][2 * q], 0x05040100u);
           else hp[q] = cvt_pk<F16>(raw[b][s][2 * q], raw[b][s][2 * q + 1]);
         }
+        // (the operands are formed before the refill below is issued: the
+        // loads can then reuse these registers, and nothing waits for them
+        // before the next chunk)
+        __asm__ volatile("" : "+v"(hp[0]), "+v"(hp[1]), "+v"(hp[2]), "+v"(hp[3]) : : "memory");
         aop[s][0] = __builtin_bit_cast(opv_t, hp);
         if constexpr (SPLIT && !BF16IN) {
           uint32_t lp[4];
@@ -445,6 +479,7 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
           for (int q = 0; q < 4; ++q)
             lp[q] = cvt_pk<F16>(raw[b][s][2 * q] - unpk_lo<F16>(hp[q]),
                                 raw[b][s][2 * q + 1] - unpk_hi<F16>(hp[q]));
+          __asm__ volatile("" : "+v"(lp[0]), "+v"(lp[1]), "+v"(lp[2]), "+v"(lp[3]) : : "memory");
           aop[s][NS - 1] = __builtin_bit_cast(opv_t, lp);
         }
       }
@@ -486,7 +521,10 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
       // weight block of chunk ch+1 (all zero past the last chunk), spread over
       // the channel blocks
 #pragma unroll
-      for (int k = kg + b * NW; k < MK; k += BPW * NW) weight(r1, wc ^ 1, k);
+      for (int q = 2 * b; q < WPT; q += 2 * BPW)
+        weight_pair(r1, wc ^ 1, kg * WPT + q);
+      // (four blocks' accumulators leave no registers for interleaving them)
+      if constexpr (BPW >= 4) __builtin_amdgcn_sched_barrier(0);
     }
     r1 = r2;
     r2 = r2 == 2 ? 0 : r2 + 1;
