@@ -7,6 +7,14 @@ using namespace cgh;
 
 bool small_c(const cg_gridder* g) { return g->nchan <= cg::kSmallC && g->prec == CG_PREC_FP32; }
 
+// The targets cover at least an eighth of the sky (a WCS grid's nominal area,
+// a HEALPix map's all of it; a list of sight lines is not known to).
+bool wide_sky(const cg_gridder* g) {
+  if (g->kind == 0)
+    return fabs(g->wcs.cdelt1 * g->wcs.cdelt2) * (double)g->ntarget >= 41253.0 / 8.0;
+  return g->healpix;
+}
+
 // Set-up of the sample-centric lookup: targets sorted by their nearest
 // RING pixel with per-ring offsets (the hash table of Sect. 2.2), and the
 // reference query disk of every ring (Sect. 3.3).  Depends only on the
@@ -161,8 +169,10 @@ cg_status run_lookup(cg_gridder* g, const double* lon, const double* lat, int64_
   } else {
     CG_HIP(cg::launch_tile_ranges(g->ntiles, g->ring_first.as<int32_t>(),
                                   g->range_off.as<uint64_t>(), g->win.as<uint32_t>(),
-                                  g->sorted_keys, w.ring_off, g->ranges.as<uint32_t>(),
-                                  g->nranges.as<uint32_t>(), g->ncand.as<uint64_t>(), st),
+                                  g->sorted_keys, n, nside, w.ring_off, wide_sky(g),
+                                  in_tmp ? w.keys : w.keys2,   // (the sort's other buffer)
+                                  g->ranges.as<uint32_t>(), g->nranges.as<uint32_t>(),
+                                  g->ncand.as<uint64_t>(), st),
            "tile ranges");
   }
   g->have_ranges = true;
@@ -465,6 +475,7 @@ cg_status cg_create_healpix(cg_gridder** out, int64_t nside, int32_t order, int6
   const int64_t ntarget = cg::hpx::npix(nside);
   cg_gridder* g = new_gridder();
   g->kind = 1;
+  g->healpix = true;
   g->ntarget = ntarget;
   g->nchan = nchan;
   g->ntiles = (ntarget + cg::kTile - 1) / cg::kTile;

@@ -191,6 +191,7 @@ struct cg_gridder {
   int device = 0;
   cgh::Allocator alloc;   // where every buffer of this handle comes from
   int kind = 0;  // 0 WCS grid, 1 sight lines
+  bool healpix = false;   // the sight lines are a HEALPix map's pixels
   cg::WcsDev wcs{};
   int64_t ntarget = 0, nchan = 0;
   int64_t tile_w = 8, tile_h = 8, ntx = 0, nty = 0, ntiles = 0, nslots = 0;

@@ -383,9 +383,12 @@ hipError_t launch_disk_ranges(const uint32_t* pk, const uint32_t* pv, int64_t np
                               int64_t ntiles, uint32_t* ranges, uint64_t* range_off,
                               uint32_t* nranges, uint64_t* ncand, hipStream_t st);
 
+// wide_sky: the targets (and so the samples that matter) cover a good part of
+// the sky; spare: n uint32 of scratch
 hipError_t launch_tile_ranges(int64_t ntiles, const int32_t* ring_first,
                               const uint64_t* range_off, const uint32_t* win,
-                              const uint32_t* keys, const uint32_t* ring_off, uint32_t* ranges,
+                              const uint32_t* keys, int64_t n, int64_t nside,
+                              const uint32_t* ring_off, bool wide_sky, uint32_t* spare, uint32_t* ranges,
                               uint32_t* nranges, uint64_t* ncand, hipStream_t st);
 // contraction kernels
 enum AccMode { ACC_OVERWRITE = 0, ACC_ADD = 1, ACC_FINAL = 2 };

@@ -387,8 +387,11 @@ hipError_t launch_tile_windows(const double* caps, const double* txyz, int64_t n
 }
 
 // ---------------------------------------------------------------------------
-// Candidate ranges of a grid call: one wavefront per tile, one window slot
-// per lane.  Two binary searches in the ring's sorted segment turn a pixel
+// Candidate ranges of a grid call: one wavefront per tile, one ring (its two
+// window slots, of which the second is empty but for rings that wrap around)
+// per lane, so that the usual tile of 30 to 64 rings is one round of
+// dependent loads, which is what bounds the kernel (one slot per lane, two
+// rounds: 10 us against 6.5 for 144 tiles).  Two binary searches in the ring's sorted segment turn a pixel
 // range into a range of sorted samples; the non-empty ones are compacted in
 // slot (ring) order as (first sorted position, first candidate index of the
 // range within the tile), and the tile's candidate count is written.
@@ -417,45 +420,76 @@ __device__ __forceinline__ void lower_bounds_u32(const uint32_t* __restrict__ ke
   *e = l2;
 }
 
+// The same for one value, within the cell of 2^shift pixels that holds it.
+__device__ __forceinline__ uint32_t lower_bound_cell(const uint32_t* __restrict__ keys,
+                                                     const uint32_t* __restrict__ cell_off, int shift,
+                                                     uint64_t v) {
+  const uint64_t c = v >> shift;
+  uint32_t lo = cell_off[c], hi = cell_off[c + 1];
+  while (lo < hi) {
+    const uint32_t mid = lo + ((hi - lo) >> 1);
+    if ((uint64_t)keys[mid] < v) lo = mid + 1;
+    else hi = mid;
+  }
+  return lo;
+}
+
+template <bool CELLS>
 __device__ __forceinline__ void tile_ranges_body(
     int64_t tile, const int32_t* __restrict__ ring_first, const uint64_t* __restrict__ range_off,
     const uint32_t* __restrict__ win, const uint32_t* __restrict__ keys,
-    const uint32_t* __restrict__ ring_off, uint32_t* __restrict__ ranges,
+    const uint32_t* __restrict__ ring_off, const uint32_t* __restrict__ cell_off, int shift, uint32_t* __restrict__ ranges,
     uint32_t* __restrict__ nranges, uint64_t* __restrict__ ncand) {
   const int lane = threadIdx.x;
   const uint64_t off = range_off[tile];
-  const int64_t ns = (int64_t)(range_off[tile + 1] - off);
+  const int64_t nring = (int64_t)(range_off[tile + 1] - off) / 2;
   const int64_t f = ring_first[tile];
-  const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   uint32_t written = 0;
   uint64_t total = 0;
-  for (int64_t s0 = 0; s0 < ns; s0 += 64) {
-    const int64_t s = s0 + lane;
-    uint32_t b = 0, e = 0;
-    if (s < ns) {
-      const uint32_t lo = win[2 * (off + s)], hi = win[2 * (off + s) + 1];
-      if (lo <= hi) {
-        const int64_t i = f + (s >> 1);
-        const uint32_t rb = ring_off[i], re = ring_off[i + 1];
-        lower_bounds_u32(keys, rb, re, (uint64_t)lo, (uint64_t)hi + 1, &b, &e);
+  for (int64_t r0 = 0; r0 < nring; r0 += 64) {
+    const int64_t r = r0 + lane;
+    uint32_t b[2] = {0, 0}, e[2] = {0, 0};
+    if (r < nring) {
+      const uint4 w = *reinterpret_cast<const uint4*>(win + 4 * (off / 2 + r));   // both windows
+      if constexpr (CELLS) {
+        if (w.x <= w.y) {
+          b[0] = lower_bound_cell(keys, cell_off, shift, w.x);
+          e[0] = lower_bound_cell(keys, cell_off, shift, (uint64_t)w.y + 1);
+        }
+        if (w.z <= w.w) {
+          b[1] = lower_bound_cell(keys, cell_off, shift, w.z);
+          e[1] = lower_bound_cell(keys, cell_off, shift, (uint64_t)w.w + 1);
+        }
+      } else {
+        const uint32_t rb = ring_off[f + r], re = ring_off[f + r + 1];
+        if (w.x <= w.y) lower_bounds_u32(keys, rb, re, (uint64_t)w.x, (uint64_t)w.y + 1, &b[0], &e[0]);
+        if (w.z <= w.w) lower_bounds_u32(keys, rb, re, (uint64_t)w.z, (uint64_t)w.w + 1, &b[1], &e[1]);
       }
     }
-    const bool h = e > b;
-    const uint64_t m = __ballot(h);
-    const uint32_t k = written + (uint32_t)__popcll(m & lt);
-    const uint32_t len = e - b;
-    uint32_t incl = len;
+    // place of the lane's ranges among the tile's, and of their candidates:
+    // the counts (at most 2 a lane) and lengths summed over the lanes before
+    const uint32_t l0 = e[0] - b[0], l1 = e[1] - b[1];
+    uint32_t cnt = (l0 ? 1u : 0u) + (l1 ? 1u : 0u), len = l0 + l1;
+    const uint32_t mycnt = cnt, mylen = len;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-      const uint32_t v = (uint32_t)__shfl_up((int)incl, o, 64);
-      if (lane >= o) incl += v;
+      const uint32_t v = (uint32_t)__shfl_up((int)len, o, 64), c = (uint32_t)__shfl_up((int)cnt, o, 64);
+      if (lane >= o) {
+        len += v;
+        cnt += c;
+      }
     }
-    if (h) {
-      ranges[2 * (off + k) + 0] = b;
-      ranges[2 * (off + k) + 1] = (uint32_t)total + (incl - len);
+    uint32_t k = written + (cnt - mycnt), at = (uint32_t)total + (len - mylen);
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (e[q] > b[q]) {
+        *reinterpret_cast<uint2*>(ranges + 2 * (off + k)) = make_uint2(b[q], at);
+        ++k;
+        at += e[q] - b[q];
+      }
     }
-    written += (uint32_t)__popcll(m);
-    total += (uint64_t)(uint32_t)__shfl((int)incl, 63, 64);
+    written += (uint32_t)__shfl((int)cnt, 63, 64);
+    total += (uint64_t)(uint32_t)__shfl((int)len, 63, 64);
   }
   if (lane == 0) {
     nranges[tile] = written;
@@ -463,12 +497,31 @@ __device__ __forceinline__ void tile_ranges_body(
   }
 }
 
+template <bool CELLS>
 __global__ void __launch_bounds__(64) k_tile_ranges(
     const int32_t* __restrict__ ring_first, const uint64_t* __restrict__ range_off,
     const uint32_t* __restrict__ win, const uint32_t* __restrict__ keys,
-    const uint32_t* __restrict__ ring_off, uint32_t* __restrict__ ranges,
-    uint32_t* __restrict__ nranges, uint64_t* __restrict__ ncand) {
-  tile_ranges_body(blockIdx.x, ring_first, range_off, win, keys, ring_off, ranges, nranges, ncand);
+    const uint32_t* __restrict__ ring_off, const uint32_t* __restrict__ cell_off, int shift,
+    uint32_t* __restrict__ ranges, uint32_t* __restrict__ nranges, uint64_t* __restrict__ ncand) {
+  tile_ranges_body<CELLS>(blockIdx.x, ring_first, range_off, win, keys, ring_off, cell_off, shift, ranges,
+                          nranges, ncand);
+}
+
+// First sorted position of every cell of 2^shift pixels.  Neighbouring threads
+// search neighbouring values, so their steps share cache lines.
+__global__ void __launch_bounds__(256) k_cell_offsets(const uint32_t* __restrict__ keys, uint32_t n,
+                                                      int shift, int64_t ncell,
+                                                      uint32_t* __restrict__ cell_off) {
+  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= ncell) return;
+  const uint64_t v = (uint64_t)c << shift;
+  uint32_t lo = 0, hi = n;
+  while (lo < hi) {
+    const uint32_t mid = lo + ((hi - lo) >> 1);
+    if ((uint64_t)keys[mid] < v) lo = mid + 1;
+    else hi = mid;
+  }
+  cell_off[c] = lo;
 }
 
 // Batches: one wavefront per tile of any job; the job's own window slots,
@@ -480,8 +533,8 @@ __global__ void __launch_bounds__(64) k_batch_tile_ranges(
   const int64_t g = blockIdx.x;
   const int j = job_of(toff, njobs, g);
   const BatchJob& jb = jobs[j];
-  tile_ranges_body(g - jb.toff, jb.ring_first, jb.range_off, jb.win, keys, ring_off + jb.ro_off,
-                   ranges + 2 * jb.rbase, nranges + jb.toff, ncand + jb.toff);
+  tile_ranges_body<false>(g - jb.toff, jb.ring_first, jb.range_off, jb.win, keys, ring_off + jb.ro_off,
+                          nullptr, 0, ranges + 2 * jb.rbase, nranges + jb.toff, ncand + jb.toff);
 }
 
 hipError_t launch_batch_tile_ranges(const BatchJob* jobs, const int64_t* toff, int njobs,
@@ -494,13 +547,38 @@ hipError_t launch_batch_tile_ranges(const BatchJob* jobs, const int64_t* toff, i
   return hipGetLastError();
 }
 
+constexpr int64_t kCellSamples = 1 << 20;
+constexpr int64_t kCellTiles = 16384;
+constexpr int64_t kCellDiv = 4;
+
 hipError_t launch_tile_ranges(int64_t ntiles, const int32_t* ring_first,
                               const uint64_t* range_off, const uint32_t* win,
-                              const uint32_t* keys, const uint32_t* ring_off, uint32_t* ranges,
+                              const uint32_t* keys, int64_t n, int64_t nside,
+                              const uint32_t* ring_off, bool wide_sky, uint32_t* spare, uint32_t* ranges,
                               uint32_t* nranges, uint64_t* ncand, hipStream_t st) {
   if (ntiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_tile_ranges, dim3((unsigned)ntiles), dim3(64), 0, st, ring_first, range_off,
-                     win, keys, ring_off, ranges, nranges, ncand);
+  // Many searches in long rings are bound by the cache lines that their steps
+  // touch (13 steps in a ring of 8000 samples).  A table of the positions of
+  // cells of pixels, at most a quarter as many as samples, leaves four or
+  // five: all-sky map of 145,800 tiles and 12 million samples 583 -> 332 us
+  // and 41 for the table, HEALPix map of 49,152 tiles and 47 million 728 ->
+  // 381 and 164 (half as many cells: 382 + 35 and 427 + 103).  Where the
+  // samples fill a small part of the sky, most cells are empty and the others
+  // as long as a ring (sight lines over 900 square degrees: 226 us + 44
+  // against 229), and few tiles or samples do not pay for the table.
+  if (wide_sky && n >= kCellSamples && ntiles >= kCellTiles) {
+    const int64_t npix = hpx::npix(nside);
+    int shift = 0;
+    while ((npix >> shift) + 2 > n / kCellDiv) ++shift;
+    const int64_t ncell = (npix >> shift) + 2;
+    hipLaunchKernelGGL(k_cell_offsets, dim3((unsigned)((ncell + 255) / 256)), dim3(256), 0, st, keys,
+                       (uint32_t)n, shift, ncell, spare);
+    hipLaunchKernelGGL(k_tile_ranges<true>, dim3((unsigned)ntiles), dim3(64), 0, st, ring_first,
+                       range_off, win, keys, ring_off, spare, shift, ranges, nranges, ncand);
+  } else {
+    hipLaunchKernelGGL(k_tile_ranges<false>, dim3((unsigned)ntiles), dim3(64), 0, st, ring_first,
+                       range_off, win, keys, ring_off, nullptr, 0, ranges, nranges, ncand);
+  }
   return hipGetLastError();
 }
 
