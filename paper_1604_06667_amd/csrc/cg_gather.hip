@@ -256,13 +256,16 @@ hipError_t launch_gather_fp32(const TileView& tv, const KernelParams& kp, const 
     // wavefront each, 15 with eight; 361 tiles of 690: 103 and 25 us); from
     // 1024 tiles on there is a wavefront per SIMD without it, and no partial
     // sums to add.
-    const bool split = tv.ntiles < 1024, sh = short_support(kp);
+    const bool split = tv.ntiles < 1024, sh = short_support(kp),
+               sinc = sinc_by_series(kp);
 #define CG_TLL(C, KT, SH, K) \
   hipLaunchKernelGGL((k_gather_tl<C, KT, SH, K>), g, b, 0, st, tv, kp, sdata, nchan, ov)
 #define CG_TLK(C, K)                                        \
   do {                                                      \
     const dim3 g((unsigned)tv.ntiles), b(64 * K);           \
-    if (kp.type >= 2) CG_TLL(C, 3, false, K);               \
+    if (sinc) CG_TLL(C, 4, true, K);                        \
+    else if (kp.type >= 2 && sh) CG_TLL(C, 3, true, K);     \
+    else if (kp.type >= 2) CG_TLL(C, 3, false, K);          \
     else if (kp.type == 0 && sh) CG_TLL(C, 0, true, K);     \
     else if (kp.type == 0) CG_TLL(C, 0, false, K);          \
     else if (sh) CG_TLL(C, 1, true, K);                     \

@@ -439,7 +439,9 @@ void launch_kt(const TileView& tv, const KernelParams& kp, const void* data, int
 #define CG_WIDE(KT, SH) \
   hipLaunchKernelGGL((k_gather_wide<CWV, KW, KT, SH, T>), g, b, 0, st, tv, kp, d, ld, nchan, vec_ok, ov)
   const bool sh = short_support(kp);
-  if (kp.type >= 2) CG_WIDE(3, false);
+  if (sinc_by_series(kp)) CG_WIDE(4, true);
+  else if (kp.type >= 2 && sh) CG_WIDE(3, true);
+  else if (kp.type >= 2) CG_WIDE(3, false);
   else if (kp.type == 0 && sh) CG_WIDE(0, true);
   else if (kp.type == 0) CG_WIDE(0, false);
   else if (sh) CG_WIDE(1, true);

@@ -263,12 +263,39 @@ __device__ __forceinline__ double radial_weight(const KernelParams& kp, double d
   return kp.tab[i] + f * (kp.tab[i + 1] - kp.tab[i]);
 }
 
+// sin(a) / a from a^2, for a up to kSincMax: the Taylor series
+// sum_k (-1)^k a^(2k) / (2k + 1)!, cut after a^24, whose next term is below
+// 3e-15 there; no term exceeds 1.8, so neither does its rounding matter in
+// the FP32 weight.  13 instructions instead of sqrt, sin and a division in
+// FP64 (HEALPix map of 25 million samples x 5: the call 8.0 -> 7.6 ms).
+constexpr double kSincMax = 3.2;
+__device__ __forceinline__ double sinc_series(double a2) {
+  double s = 1.0 / 15511210043330985984000000.0;           // 1 / 25!
+  s = fma(s, a2, -1.0 / 25852016738884976640000.0);         // 23!
+  s = fma(s, a2, 1.0 / 51090942171709440000.0);             // 21!
+  s = fma(s, a2, -1.0 / 121645100408832000.0);              // 19!
+  s = fma(s, a2, 1.0 / 355687428096000.0);                  // 17!
+  s = fma(s, a2, -1.0 / 1307674368000.0);                   // 15!
+  s = fma(s, a2, 1.0 / 6227020800.0);                       // 13!
+  s = fma(s, a2, -1.0 / 39916800.0);                        // 11!
+  s = fma(s, a2, 1.0 / 362880.0);                           // 9!
+  s = fma(s, a2, -1.0 / 5040.0);
+  s = fma(s, a2, 1.0 / 120.0);
+  s = fma(s, a2, -1.0 / 6.0);
+  return fma(s, a2, 1.0);
+}
+
 // The kernel type and the distance form of a launch, fixed at compile time so
 // that the loops over pairs carry no branch for them: KT 0 circular Gaussian,
-// 1 elliptical, 3 one of the radial shapes (chosen at run time); SHORT: a
-// support of at most ~0.57 deg (short_support).
+// 1 elliptical, 3 one of the radial shapes (chosen at run time), 4 the
+// tapered sinc by its series (short supports that end by kSincMax, in the
+// usual case at its first zero, pi); SHORT: a support of at most ~0.57 deg
+// (short_support).
 __host__ __device__ __forceinline__ bool short_support(const KernelParams& kp) {
   return kp.cs2 <= 1e-4;
+}
+inline bool sinc_by_series(const KernelParams& kp) {
+  return kp.type == 2 && short_support(kp) && kp.ks * 2.0 * asin(0.5 * sqrt(kp.cs2)) <= kSincMax;
 }
 template <int KT, bool SHORT>
 __device__ __forceinline__ float pair_weight(const KernelParams& kp, double c2, double dx, double dy,
@@ -278,6 +305,8 @@ __device__ __forceinline__ float pair_weight(const KernelParams& kp, double c2, 
   // 1.1e-10 relative, in two FP64 operations
   const double d2 = SHORT ? fma(c2 * c2, 1.0 / 12.0, c2) : chord2_to_d2(c2);
   if constexpr (KT == 3) return (float)radial_weight(kp, d2);
+  if constexpr (KT == 4)
+    return (float)((double)exp2_neg(d2 * kp.k1) * sinc_series(kp.ks * kp.ks * d2));
   if constexpr (KT == 0) return exp2_neg(d2 * kp.k1);
   const double u = dx * ax + dy * ay + dz * az;
   if constexpr (SHORT) {

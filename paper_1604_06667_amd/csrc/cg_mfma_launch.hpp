@@ -42,7 +42,9 @@ static void launch_cfg(const TileView& tv, const KernelParams& kp, const void* d
       hipLaunchKernelGGL((k_gather_mfma<NW, BPW, KT_, SH_, MODE, false, T, KS>), g, b, 0, st, tv, kp, \
                          d, z, ld, nchan, ov);                                                  \
   } while (0)
-  if (kp.type >= 2) CG_MFMA_LAUNCH(3, false);
+  if (sinc_by_series(kp)) CG_MFMA_LAUNCH(4, true);
+  else if (kp.type >= 2 && sh) CG_MFMA_LAUNCH(3, true);
+  else if (kp.type >= 2) CG_MFMA_LAUNCH(3, false);
   else if (kp.type == 0 && sh) CG_MFMA_LAUNCH(0, true);
   else if (kp.type == 0) CG_MFMA_LAUNCH(0, false);
   else if (sh) CG_MFMA_LAUNCH(1, true);

@@ -146,7 +146,8 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
   const int kh = lane >> 5;      // which 8 samples of the chunk this lane holds
   const int64_t cbase = c0 + wv * BPW * 32 + cl;   // this lane's channel in block 0
   // KT: 0 gauss1d, 1 gauss2d, 2 either, chosen at run time (batched jobs of
-  // both types), 3 a radial kernel of arbitrary shape (tapered sinc or
+  // both types), 4 the tapered sinc by its series (sinc_by_series), 3 any
+  // other radial kernel (tapered sinc or
   // tabulated profile, chosen at run time).  SHORT: the support of the launch
   // (of every job) is at most ~0.57 deg, so that the weights carry no branch
   // and no call for longer chords (whose call convention alone held the
@@ -311,7 +312,11 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
              c * (1.0f / 3150.0f + c * (1.0f / 16632.0f)))));
     };
     float w;
-    if constexpr (KT == 3) {
+    if constexpr (KT == 4) {
+      const double d2 = fma(c2 * c2, 1.0 / 12.0, c2);
+      const float v = (float)((double)exp2_neg(d2 * kp.k1) * sinc_series(kp.ks * kp.ks * d2));
+      w = c2 <= kp.cs2 ? v : 0.0f;
+    } else if constexpr (KT == 3) {
       // radial kernels of arbitrary shape: the tapered sinc, or the
       // tabulated profile interpolated linearly (zero past its last point)
       const float d2 = c * (1.0f + series());
@@ -387,7 +392,12 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
   // this lane's A-operand values (raw input) of one chunk
   // 16-bit input of the operand's own type is used bit for bit; any other input is converted through FP32.
   constexpr bool DIRECT = (BF16IN && !F16) || (std::is_same<T, _Float16>::value && F16);
-  using raw_t = typename std::conditional<DIRECT, uint32_t, float>::type;
+  // (held as delivered until they are used: a conversion at the load would
+  // wait for it; but four blocks of FP64 values do not fit the registers)
+  constexpr bool RAW16 = sizeof(T) == 2;
+  constexpr bool RAW64 = sizeof(T) == 8 && BPW * KS <= 2;
+  using raw_t = typename std::conditional<RAW16, uint32_t,
+                typename std::conditional<RAW64, double, float>::type>::type;
   raw_t raw[BPW][KS][8];
   // Lanes whose channel lies past cend read the last valid channel of the
   // same row instead, so that every address stays inside the caller's row (or
@@ -398,18 +408,22 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
       const int64_t* rw = &s_row[rb][16 * s + 8 * kh];
-      if constexpr (DIRECT) {
-        const uint16_t* d16 = reinterpret_cast<const uint16_t*>(data);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) raw[b][s][i] = (uint32_t)ldg<GL>(d16, rw[i] + cofs);
-      } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < 8; ++i) {
+        if constexpr (RAW16) {
+          raw[b][s][i] = (uint32_t)ldg<GL>(reinterpret_cast<const uint16_t*>(data), rw[i] + cofs);
+        } else {
           const T v = ldg<GL>(data, rw[i] + cofs);
-          raw[b][s][i] = in_f32<T>(&v);
+          if constexpr (RAW64) raw[b][s][i] = v;
+          else raw[b][s][i] = in_f32<T>(&v);
         }
       }
     }
+  };
+  // value i of a block's step as FP32
+  auto raw_f32 = [&](int b, int s, int i) -> float {
+    if constexpr (RAW16) return from_bits<!BF16IN>((uint16_t)raw[b][s][i]);
+    else return (float)raw[b][s][i];
   };
 
   // prologue: records of chunks 0, 1 in LDS, of chunk 2 in registers; the
@@ -462,11 +476,16 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
         uint32_t hp[4];
+        float x[8];
+        if constexpr (!DIRECT) {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) x[i] = raw_f32(b, s, i);
+        }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           if constexpr (DIRECT)   // (packed only here, so that the loads stay in flight until now)
             hp[q] = __builtin_amdgcn_perm(raw[b][s][2 * q + 1], raw[b][s][2 * q], 0x05040100u);
-          else hp[q] = cvt_pk<F16>(raw[b][s][2 * q], raw[b][s][2 * q + 1]);
+          else hp[q] = cvt_pk<F16>(x[2 * q], x[2 * q + 1]);
         }
         // (the operands are formed before the refill below is issued: the
         // loads can then reuse these registers, and nothing waits for them
@@ -477,8 +496,7 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
           uint32_t lp[4];
 #pragma unroll
           for (int q = 0; q < 4; ++q)
-            lp[q] = cvt_pk<F16>(raw[b][s][2 * q] - unpk_lo<F16>(hp[q]),
-                                raw[b][s][2 * q + 1] - unpk_hi<F16>(hp[q]));
+            lp[q] = cvt_pk<F16>(x[2 * q] - unpk_lo<F16>(hp[q]), x[2 * q + 1] - unpk_hi<F16>(hp[q]));
           __asm__ volatile("" : "+v"(lp[0]), "+v"(lp[1]), "+v"(lp[2]), "+v"(lp[3]) : : "memory");
           aop[s][NS - 1] = __builtin_bit_cast(opv_t, lp);
         }

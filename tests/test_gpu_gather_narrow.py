@@ -32,13 +32,14 @@ def test_channel_edges(nx, ny, n, nchan):
 # support in pixels of 1': well below a pixel, and (600': the long distance
 # series) far above a tile; a table and the elliptical kernel in both
 @pytest.mark.parametrize("support", [0.05, 0.7, 60.0, 600.0])
-@pytest.mark.parametrize("kind", ["gauss1d", "gauss2d", "tapered_sinc", "table"])
+@pytest.mark.parametrize("kind", ["gauss1d", "gauss2d", "tapered_sinc", "two_zeros", "table"])
 @pytest.mark.parametrize("nx", [20, 257])
 def test_supports_and_kernels(support, kind, nx):
     import dataclasses
     s = support / 60.0
     kernel = {"gauss1d": ("gauss1d", (s / 3.0,)), "gauss2d": ("gauss2d", (s / 3.0, s / 4.5, 30.0)),
               "tapered_sinc": ("tapered_sinc", (s / 3.0, s)),
+              "two_zeros": ("tapered_sinc", (s / 3.0, s / 2.0)),   # sinc beyond its first zero
               "table": ("table", (s, 1.0, 0.8, 0.4, 0.1, 0.0))}[kind]
     n = 4000 if support < 100.0 or nx < 100 else 150
     wl = _field(nx, nx, n, 2, kernel=kernel)

@@ -8,7 +8,7 @@ import pytest
 
 import oracle
 from gpu_util import flat, make_gridder, say, to_device
-from test_gpu_gather_wide import _field
+from test_gpu_gather_wide import _field, check_signed
 
 pytestmark = pytest.mark.gpu
 TOL = 2e-3          # the matrix-core precisions' bound
@@ -16,6 +16,8 @@ TOLW = 1e-6
 
 
 def _check(cube, w, wl, ref):
+    if wl.kernel[0] == "tapered_sinc" and wl.kernel[1][1] < wl.support:
+        return check_signed(cube, w, wl, ref, TOL)
     ev = oracle.e_val(flat(cube, wl.nchan), ref["R"], ref["W"])
     ew = oracle.e_weights(w.cpu().numpy().astype(np.float64).ravel(), ref["W"])
     say(f"  e_val={ev:.2e} e_W={ew:.2e}")
@@ -23,11 +25,11 @@ def _check(cube, w, wl, ref):
 
 
 @pytest.mark.parametrize("nchan", [1, 31, 33, 64, 65, 128, 129, 256, 257, 512, 513])
-@pytest.mark.parametrize("dtype", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("dtype", ["f32", "f64", "bf16", "f16"])
 def test_channel_edges(nchan, dtype):
     import torch
     wl = _field(33, 17, 900, nchan)
-    dt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dtype]
+    dt = {"f32": torch.float32, "f64": torch.float64, "bf16": torch.bfloat16, "f16": torch.float16}[dtype]
     wl = dataclasses.replace(wl, data=wl.data.to(dt), dtype=dtype)
     ref = oracle.grid_workload(dataclasses.replace(wl, data=wl.data.to(torch.float64), dtype="f64"))
     lon, lat, d = to_device(wl)
@@ -37,12 +39,14 @@ def test_channel_edges(nchan, dtype):
 
 
 def _kernel(kind, s):
-    return (kind, (s / 3.0,)) if kind == "gauss1d" else (kind, (s / 3.0, s / 4.5, 30.0))
+    return {"gauss1d": ("gauss1d", (s / 3.0,)), "gauss2d": ("gauss2d", (s / 3.0, s / 4.5, 30.0)),
+            "tapered_sinc": ("tapered_sinc", (s / 3.0, s)), "two_zeros": ("tapered_sinc", (s / 3.0, s / 2.0)),
+            "table": ("table", (s, 1.0, 0.8, 0.4, 0.1, 0.0))}[kind]
 
 
 # 0.57 deg divides the short-support form from the general one
 @pytest.mark.parametrize("support", [0.075, 0.57, 0.58, 10.0])
-@pytest.mark.parametrize("kind", ["gauss1d", "gauss2d"])
+@pytest.mark.parametrize("kind", ["gauss1d", "gauss2d", "tapered_sinc", "two_zeros", "table"])
 @pytest.mark.parametrize("nchan", [40, 300])
 def test_support_forms(support, kind, nchan):
     wl = _field(33, 17, 700, nchan, kernel=_kernel(kind, support))
