@@ -41,7 +41,7 @@ cg_status ensure_disk(cg_gridder* g, hipStream_t st) {
   CG_HIP(cg::radix_sort(g->dk_tkeys.as<uint32_t>(), g->dk_tvals.as<uint32_t>(),
                         g->dk_tkeys2.as<uint32_t>(), g->dk_tvals2.as<uint32_t>(),
                         g->dk_thist.as<uint32_t>(), nsl, bits_for((uint64_t)cg::hpx::npix(nside)),
-                        &in_tmp, st),
+                        false, &in_tmp, st),
          "sort targets");
   g->dk_tk = in_tmp ? g->dk_tkeys2.as<uint32_t>() : g->dk_tkeys.as<uint32_t>();
   g->dk_ts = in_tmp ? g->dk_tvals2.as<uint32_t>() : g->dk_tvals.as<uint32_t>();
@@ -120,7 +120,7 @@ cg_status run_disk_lookup(cg_gridder* g, int64_t n, hipStream_t st) {
   bool in_tmp = false;
   CG_HIP(cg::radix_sort(g->dk_pk.as<uint32_t>(), g->dk_pv.as<uint32_t>(), g->dk_pk2.as<uint32_t>(),
                         g->dk_pv2.as<uint32_t>(), g->dk_phist.as<uint32_t>(), np,
-                        bits_for((uint64_t)nt), &in_tmp, st),
+                        bits_for((uint64_t)nt), false, &in_tmp, st),
          "sort pairs");
   const uint32_t* pk = in_tmp ? g->dk_pk2.as<uint32_t>() : g->dk_pk.as<uint32_t>();
   const uint32_t* pv = in_tmp ? g->dk_pv2.as<uint32_t>() : g->dk_pv.as<uint32_t>();
@@ -148,12 +148,12 @@ cg_status run_lookup(cg_gridder* g, const double* lon, const double* lat, int64_
   workspace_layout(n, nside, with_data ? g->nchan : 0, base, &g->ws);
   Workspace& w = g->ws;
   const int npack = with_data && g->nchan <= 2 ? (int)g->nchan : 0;
-  CG_HIP(cg::launch_prep(lon, lat, n, nside, w.keys, w.vals, g->flag.as<int>(), w.rec, data,
+  CG_HIP(cg::launch_prep(lon, lat, n, nside, w.keys, g->flag.as<int>(), w.rec, data,
                          dtype, ld, npack, st),
          "prep");
   bool in_tmp = false;
   const int bits = bits_for((uint64_t)cg::hpx::npix(nside));
-  CG_HIP(cg::radix_sort(w.keys, w.vals, w.keys2, w.vals2, w.hist, n, bits, &in_tmp, st),
+  CG_HIP(cg::radix_sort(w.keys, w.vals, w.keys2, w.vals2, w.hist, n, bits, true, &in_tmp, st),
          "radix sort");
   g->sorted_keys = in_tmp ? w.keys2 : w.keys;
   g->sorted_vals = in_tmp ? w.vals2 : w.vals;
@@ -442,7 +442,7 @@ cg_status cg_create_sightlines(cg_gridder** out, const double* lon_deg, const do
     if (e == hipSuccess)
       e = cg::radix_sort(k1.as<uint32_t>(), v1.as<uint32_t>(), k2.as<uint32_t>(),
                          v2.as<uint32_t>(), h.as<uint32_t>(), ntarget,
-                         bits_for((uint64_t)cg::hpx::npix(8192)), &in_tmp, st);
+                         bits_for((uint64_t)cg::hpx::npix(8192)), false, &in_tmp, st);
     if (e == hipSuccess)
       e = cg::launch_sl_targets(lon_deg, lat_deg, in_tmp ? v2.as<uint32_t>() : v1.as<uint32_t>(),
                                 ntarget, g->nslots, g->txyz.as<double>(), g->tll.as<double>(),

@@ -276,7 +276,7 @@ cg_status lookup_part(cg_batch* b, hipStream_t st) {
   bool in_tmp = false;
   CG_HIP(cg::radix_sort_jobs(b->keys.as<uint32_t>(), b->vals.as<uint32_t>(),
                              b->keys2.as<uint32_t>(), b->vals2.as<uint32_t>(),
-                             b->hist.as<uint32_t>(), b->ntot, b->bits, dev_noff(b), njobs,
+                             b->hist.as<uint32_t>(), b->ntot, b->bits, false, dev_noff(b), njobs,
                              &in_tmp, st),
          "batch sort");
   b->sorted_in_tmp = in_tmp;

@@ -38,8 +38,9 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 // roundings), so the marks are a superset and the FP64 test alone decides.
 // Marking with an FP64 dot product per pair and lane took half of the
 // kernel's vector instructions (47.2 million samples x 2 onto nside 512: 3.74
-// ms, 3.35 with these marks and the kernel type fixed at compile time; 12
-// million x 8 onto 4320 x 2160: 3.31 and 2.43 ms).
+// ms, 3.35 with these marks and the kernel type fixed at compile time, and
+// 2.57 with the two channels read from the record instead of an array of
+// their own; 12 million x 8 onto 4320 x 2160: 3.31 and 2.43 ms).
 template <int CMAX, int KT, bool SHORT, int KW>
 __global__ void __launch_bounds__(64 * KW, CMAX <= 8 && KT != 3 && SHORT ? 5 : 4) k_gather_tl(TileView tv, KernelParams kp,
                                                        const float* __restrict__ sdata,
@@ -147,8 +148,14 @@ __global__ void __launch_bounds__(64 * KW, CMAX <= 8 && KT != 3 && SHORT ? 5 : 4
       lr = tv.srec[pos];
       // every slot of the row is set (zeros past nchan), so the walk reads
       // and multiplies all CMAX slots without a branch per channel
+      if constexpr (CMAX <= 2) {   // carried in the record
+        const uint64_t d = (uint64_t)__double_as_longlong(lr.w);
+        ld[0] = __uint_as_float((uint32_t)d);
+        if (CMAX > 1) ld[CMAX - 1] = __uint_as_float((uint32_t)(d >> 32));
+      } else {
 #pragma unroll
-      for (int c = 0; c < CMAX; ++c) ld[c] = c < nchan ? sdata[pos * nchan + c] : 0.0f;
+        for (int c = 0; c < CMAX; ++c) ld[c] = c < nchan ? sdata[pos * nchan + c] : 0.0f;
+      }
     }
   };
   fetch(kw);

@@ -47,7 +47,8 @@ struct TileView {
   int64_t ntx;                 // tiles per row of a WCS grid (0: sight lines)
   // the sorted samples the ranges point into: one 32-byte record each, the
   // unit vector and (as the bits of the fourth double) the sample's row,
-  // i.e. its index in the caller's input (in a batch, the job's input)
+  // i.e. its index in the caller's input (in a batch, the job's input; in a
+  // narrow FP32 grid of one or two channels, those)
   const double4* srec;
 };
 
@@ -354,14 +355,18 @@ __device__ __forceinline__ void wave_lds_order() {
 
 // rec: 4 doubles per sample (unit vector; channels 0-1 as FP32 when npack > 0)
 hipError_t launch_prep(const double* lon, const double* lat, int64_t n, int64_t nside,
-                       uint32_t* keys, uint32_t* vals, int* flag, double* rec, const void* data,
+                       uint32_t* keys, int* flag, double* rec, const void* data,
                        int dtype, int64_t ld, int npack, hipStream_t st);
+// iota: the values are 0, 1, 2, ... and vals need not be set
 hipError_t radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp,
-                      uint32_t* hist, int64_t n, int bits, bool* result_in_tmp, hipStream_t st);
+                      uint32_t* hist, int64_t n, int bits, bool iota, bool* result_in_tmp,
+                      hipStream_t st);
 size_t radix_hist_elems(int64_t n);   // histogram and digit totals
 hipError_t launch_ring_offsets(const uint32_t* keys, int64_t n, int64_t nside, uint32_t* ring_off,
                                hipStream_t st);
-// srec: one record per sorted sample (unit vector, input row as int64 bits)
+// srec: one record per sorted sample (unit vector; input row as int64 bits, or
+// with data and npack > 0 the channels 0-1 as FP32); sdata: the rows of narrow
+// FP32 grids of more channels
 hipError_t launch_permute(const uint32_t* vals, const uint32_t* nvalid_dev, int64_t n,
                           const double* rec, const void* data, int dtype, int64_t ld,
                           int64_t nchan, bool with_data, int npack, double* srec,
@@ -496,8 +501,8 @@ hipError_t launch_batch_prep(const BatchJob* jobs, const int64_t* noff, int njob
 // the job of each value (values are positions in the concatenated order), so
 // the result is job-major and sorted by key within each job.
 hipError_t radix_sort_jobs(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp,
-                           uint32_t* hist, int64_t n, int bits, const int64_t* noff, int njobs,
-                           bool* result_in_tmp, hipStream_t st);
+                           uint32_t* hist, int64_t n, int bits, bool iota, const int64_t* noff,
+                           int njobs, bool* result_in_tmp, hipStream_t st);
 hipError_t launch_batch_ring_offsets(const BatchJob* jobs, const int64_t* rooff, int njobs,
                                      int64_t nentries, const uint32_t* keys, uint32_t* ring_off,
                                      hipStream_t st);

@@ -26,16 +26,15 @@ __device__ __forceinline__ float to_f32<uint16_t>(const uint16_t* p, int64_t i) 
 template <>
 __device__ __forceinline__ float to_f32<_Float16>(const _Float16* p, int64_t i) { return (float)p[i]; }
 
-// HEALPix RING key and value (the sample's own index) of every sample, and
-// its record in input order: the unit vector and, when the cube has at most
+// HEALPix RING key of every sample (its value in the sort is its own index,
+// which the first pass forms by itself), and its record in input order: the unit vector and, when the cube has at most
 // two channels, the channels as FP32 in the fourth word.  The permutation
 // after the sort then reads one 32-byte record per sample instead of the
 // separate longitude, latitude and data rows.
 template <typename T>
 __global__ void __launch_bounds__(256) k_prep(const double* __restrict__ lon,
                                               const double* __restrict__ lat, int64_t n,
-                                              int64_t nside, uint32_t* __restrict__ keys,
-                                              uint32_t* __restrict__ vals, int* flag,
+                                              int64_t nside, uint32_t* __restrict__ keys, int* flag,
                                               double4* __restrict__ rec,
                                               const T* __restrict__ data, int64_t ld, int npack) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -67,31 +66,30 @@ __global__ void __launch_bounds__(256) k_prep(const double* __restrict__ lon,
                                            (uint64_t)__float_as_uint(d0)));
   }
   keys[i] = key;
-  vals[i] = (uint32_t)i;
   rec[i] = r;
 }
 
 hipError_t launch_prep(const double* lon, const double* lat, int64_t n, int64_t nside,
-                       uint32_t* keys, uint32_t* vals, int* flag, double* rec, const void* data,
+                       uint32_t* keys, int* flag, double* rec, const void* data,
                        int dtype, int64_t ld, int npack, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   const dim3 grid((unsigned)((n + 255) / 256)), blk(256);
   double4* r = reinterpret_cast<double4*>(rec);
   switch (dtype) {
     case 0:
-      hipLaunchKernelGGL(k_prep<double>, grid, blk, 0, st, lon, lat, n, nside, keys, vals, flag, r,
+      hipLaunchKernelGGL(k_prep<double>, grid, blk, 0, st, lon, lat, n, nside, keys, flag, r,
                          (const double*)data, ld, npack);
       break;
     case 1:
-      hipLaunchKernelGGL(k_prep<float>, grid, blk, 0, st, lon, lat, n, nside, keys, vals, flag, r,
+      hipLaunchKernelGGL(k_prep<float>, grid, blk, 0, st, lon, lat, n, nside, keys, flag, r,
                          (const float*)data, ld, npack);
       break;
     case 2:
-      hipLaunchKernelGGL(k_prep<_Float16>, grid, blk, 0, st, lon, lat, n, nside, keys, vals, flag,
+      hipLaunchKernelGGL(k_prep<_Float16>, grid, blk, 0, st, lon, lat, n, nside, keys, flag,
                          r, (const _Float16*)data, ld, npack);
       break;
     default:
-      hipLaunchKernelGGL(k_prep<uint16_t>, grid, blk, 0, st, lon, lat, n, nside, keys, vals, flag,
+      hipLaunchKernelGGL(k_prep<uint16_t>, grid, blk, 0, st, lon, lat, n, nside, keys, flag,
                          r, (const uint16_t*)data, ld, npack);
       break;
   }
@@ -204,7 +202,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_sort_small(
     const int i = first + 64 * r;
     const bool ok = r < nr && i < n;
     key[r] = ok ? kin[i] : 0u;
-    val[r] = ok ? vin[i] : 0u;
+    val[r] = ok ? (vin ? vin[i] : (uint32_t)i) : 0u;
   }
   for (int p = 0; p < npass; ++p) {
     const int shift = p * NBITS;
@@ -275,14 +273,17 @@ __global__ void __launch_bounds__(kSortThreads) k_hist(const uint32_t* __restric
   stage_job_offsets<JOB>(s_off, joff, njobs);
   __syncthreads();
   const int64_t base = (int64_t)blockIdx.x * (kSortThreads * ITEMS);
+  // (all loads first: none of them waits for another pair's count)
+  uint32_t in[ITEMS];
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r) {
     const int64_t i = base + (int64_t)r * kSortThreads + t;
-    if (i < n) {
-      const uint32_t d = sort_digit<JOB, NBITS>(JOB ? 0u : keys[i], JOB ? vals[i] : 0u, shift, s_off, njobs);
-      atomicAdd(&h[d], 1u);
-    }
+    in[r] = i < n ? (JOB ? vals[i] : keys[i]) : 0u;
   }
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r)
+    if (base + (int64_t)r * kSortThreads + t < n)
+      atomicAdd(&h[sort_digit<JOB, NBITS>(in[r], in[r], shift, s_off, njobs)], 1u);
   __syncthreads();
   for (int q = t; q < BINS; q += kSortThreads) hist[(int64_t)q * nblocks + blockIdx.x] = h[q];
 }
@@ -348,7 +349,7 @@ __global__ void __launch_bounds__(kSortThreads) k_scatter(
   for (int r = 0; r < ITEMS; ++r) {
     const int64_t i = first + 64 * r;
     key[r] = i < n ? kin[i] : 0u;
-    val[r] = i < n ? vin[i] : 0u;
+    val[r] = i < n ? (vin ? vin[i] : (uint32_t)i) : 0u;
   }
   for (int q = t; q < NW * BINS / 2; q += kSortThreads) reinterpret_cast<uint32_t*>(&s_cnt[0][0])[q] = 0u;
   stage_job_offsets<JOB>(s_off, joff, njobs);
@@ -471,16 +472,17 @@ static void sort_pass_items(const uint32_t* ki, const uint32_t* vi, uint32_t* ko
 }
 
 hipError_t radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp,
-                      uint32_t* hist, int64_t n, int bits, bool* result_in_tmp, hipStream_t st) {
-  return radix_sort_jobs(keys, vals, keys_tmp, vals_tmp, hist, n, bits, nullptr, 0, result_in_tmp,
-                         st);
+                      uint32_t* hist, int64_t n, int bits, bool iota, bool* result_in_tmp,
+                      hipStream_t st) {
+  return radix_sort_jobs(keys, vals, keys_tmp, vals_tmp, hist, n, bits, iota, nullptr, 0,
+                         result_in_tmp, st);
 }
 
 hipError_t radix_sort_jobs(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp,
-                           uint32_t* hist, int64_t n, int bits, const int64_t* noff, int njobs,
-                           bool* result_in_tmp, hipStream_t st) {
+                           uint32_t* hist, int64_t n, int bits, bool iota, const int64_t* noff,
+                           int njobs, bool* result_in_tmp, hipStream_t st) {
   *result_in_tmp = false;
-  if (n <= 1) return hipSuccess;
+  if (n < 1 || (n == 1 && !iota)) return hipSuccess;
   if (njobs > kMaxJobs) return hipErrorInvalidValue;
   uint32_t *ki = keys, *vi = vals, *ko = keys_tmp, *vo = vals_tmp;
   bool in_tmp = false;
@@ -492,15 +494,20 @@ hipError_t radix_sort_jobs(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, u
   const int npass = bits > 0 ? (bits + kDigitBits - 1) / kDigitBits : 0;
   const int db = npass > 0 ? (bits + npass - 1) / npass : 8;   // bits per digit
   if (npass > 0 && n <= kSmallSort) {
-    if (db <= 8) hipLaunchKernelGGL(k_sort_small<8>, dim3(1), dim3(kSmallThreads), 0, st, ki, vi, (int)n, npass, ko, vo);
-    else if (db == 9) hipLaunchKernelGGL(k_sort_small<9>, dim3(1), dim3(kSmallThreads), 0, st, ki, vi, (int)n, npass, ko, vo);
-    else hipLaunchKernelGGL(k_sort_small<10>, dim3(1), dim3(kSmallThreads), 0, st, ki, vi, (int)n, npass, ko, vo);
+    const int np = n == 1 ? 1 : npass;
+    if (db <= 8) hipLaunchKernelGGL(k_sort_small<8>, dim3(1), dim3(kSmallThreads), 0, st, ki,
+                                     iota ? nullptr : vi, (int)n, np, ko, vo);
+    else if (db == 9) hipLaunchKernelGGL(k_sort_small<9>, dim3(1), dim3(kSmallThreads), 0, st, ki,
+                                     iota ? nullptr : vi, (int)n, np, ko, vo);
+    else hipLaunchKernelGGL(k_sort_small<10>, dim3(1), dim3(kSmallThreads), 0, st, ki,
+                                     iota ? nullptr : vi, (int)n, np, ko, vo);
     flip();
   } else {
     for (int p = 0; p < npass; ++p) {
-      if (db <= 8) sort_pass_items<false, 8>(ki, vi, ko, vo, hist, n, 8 * p, noff, njobs, st);
-      else if (db == 9) sort_pass_items<false, 9>(ki, vi, ko, vo, hist, n, 9 * p, noff, njobs, st);
-      else sort_pass_items<false, 10>(ki, vi, ko, vo, hist, n, 10 * p, noff, njobs, st);
+      const uint32_t* in = iota && p == 0 ? nullptr : vi;
+      if (db <= 8) sort_pass_items<false, 8>(ki, in, ko, vo, hist, n, 8 * p, noff, njobs, st);
+      else if (db == 9) sort_pass_items<false, 9>(ki, in, ko, vo, hist, n, 9 * p, noff, njobs, st);
+      else sort_pass_items<false, 10>(ki, in, ko, vo, hist, n, 10 * p, noff, njobs, st);
       flip();
     }
   }
@@ -643,8 +650,13 @@ hipError_t launch_ring_offsets(const uint32_t* keys, int64_t n, int64_t nside, u
 }
 
 // ---------------------------------------------------------------------------
-// permute: sorted unit vectors (SoA) and, for narrow cubes, the data rows in
-// sorted order converted to FP32 (so the gather streams contiguous rows).
+// permute: sorted records (unit vector and input row, or the one or two
+// channels of a narrow FP32 grid) and, for narrow cubes of more channels, the
+// data rows in sorted order converted to FP32 (so the gather streams
+// contiguous rows).  Bound by the cache line per record that the random read
+// takes: 1.5 ms for 47.2 million records (1.6 with non-temporal loads).  Rows
+// stored behind their unit vectors, one stretch per sample, cost more here
+// than the gather gained: 12 million x 8 channels 0.77 -> 0.91 ms.
 
 template <typename T, bool VEC4>
 __global__ void __launch_bounds__(256) k_permute(const uint32_t* __restrict__ vals,
@@ -659,14 +671,13 @@ __global__ void __launch_bounds__(256) k_permute(const uint32_t* __restrict__ va
   if (p >= nvalid) return;
   const int64_t src = vals[p];
   const double4 r = rec[src];
+  if (with_data && npack > 0) {
+    srec[p] = r;   // one or two channels stay in the record
+    return;
+  }
   srec[p] = make_double4(r.x, r.y, r.z, __longlong_as_double(src));
   if (with_data) {
-    if (npack > 0) {
-      // channels carried in the record
-      const uint64_t b = (uint64_t)__double_as_longlong(r.w);
-      sdata[p * nchan] = __uint_as_float((uint32_t)b);
-      if (npack > 1) sdata[p * nchan + 1] = __uint_as_float((uint32_t)(b >> 32));
-    } else if constexpr (VEC4) {
+    if constexpr (VEC4) {
       // FP32 rows with nchan and ld multiples of 4 and 16-byte aligned: whole
       // 16-byte pieces per load and store
       const float4* in = reinterpret_cast<const float4*>(data + src * ld);
