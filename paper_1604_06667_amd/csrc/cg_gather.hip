@@ -42,13 +42,18 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 // 2.57 with the two channels read from the record instead of an array of
 // their own; 12 million x 8 onto 4320 x 2160: 3.31 and 2.43 ms).
 template <int CMAX, int KT, bool SHORT, int KW>
-__global__ void __launch_bounds__(64 * KW, CMAX <= 8 && KT != 3 && SHORT ? 5 : 4) k_gather_tl(TileView tv, KernelParams kp,
+__global__ void __launch_bounds__(64 * KW, CMAX <= 4 && KT != 3 && SHORT ? 5 : 4) k_gather_tl(TileView tv, KernelParams kp,
                                                        const float* __restrict__ sdata,
                                                        int64_t nchan, OutView ov) {
   // per wavefront: unit vectors, data rows and (u, v, u^2 + v^2, 1) of a chunk
+  // rows of 4 channels and more are padded by 16 bytes: at 64 or 128 bytes the
+  // lanes' rows fell on 4 or 2 groups of LDS banks (the LDS was busy 85 % of
+  // the kernel; 12 million samples x 8: the call 3.59 -> 3.43 ms, 2 million x 16
+  // onto 1000 x 1000: 1.82 -> 1.14 ms; FP32 rows in LDS: 3.53 and 1.12 ms)
+  constexpr int DS = CMAX >= 4 ? CMAX + 2 : CMAX;
   struct Chunk {
     double x[kChunk], y[kChunk], z[kChunk];
-    double d[kChunk * CMAX];
+    double d[kChunk * DS];
     float4 q[kChunk];
   };
   __shared__ Chunk s_chunk[KW];
@@ -168,7 +173,7 @@ __global__ void __launch_bounds__(64 * KW, CMAX <= 8 && KT != 3 && SHORT ? 5 : 4
       const float v = (float)(lr.x * fx + lr.y * fy + lr.z * fz);
       sc.q[lane] = make_float4(u, v, u * u + v * v, 1.0f);
 #pragma unroll
-      for (int c = 0; c < CMAX; ++c) sc.d[lane * CMAX + c] = (double)ld[c];
+      for (int c = 0; c < CMAX; ++c) sc.d[lane * DS + c] = (double)ld[c];
     } else {
       sc.q[lane] = make_float4(0.0f, 0.0f, 1e30f, 1.0f);   // no candidate: never marked
     }
@@ -213,7 +218,7 @@ __global__ void __launch_bounds__(64 * KW, CMAX <= 8 && KT != 3 && SHORT ? 5 : 4
                                                         bx[0], bx[1], bx[2]);
         wacc += w;
 #pragma unroll
-        for (int c = 0; c < CMAX; ++c) acc[c] = fma(w, sc.d[k * CMAX + c], acc[c]);
+        for (int c = 0; c < CMAX; ++c) acc[c] = fma(w, sc.d[k * DS + c], acc[c]);
       }
     }
     wave_lds_order();
