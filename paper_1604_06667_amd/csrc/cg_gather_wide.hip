@@ -457,8 +457,13 @@ void launch_shape(const TileView& tv, const KernelParams& kp, const void* data, 
   // each) without work, 64-channel workgroups whose four wavefronts split
   // the candidates (eight scans of 40,000 samples x 60 channels, elliptical
   // beam, onto 301 x 257 pixels: 4.3 ms against 9.2 ms in the vector form).
+  // Where even those leave CUs empty, eight wavefronts split them (9 tiles x
+  // 400 channels: the call 139 us with four, 111 with eight; with two
+  // workgroups of four to a CU, four are the better: 250,000 pixels x 60
+  // channels 0.83 ms against 0.90).
   const bool few = tv.ntiles * ((nchan + 255) / 256) < 512;
-  if (nchan <= 64 || few) launch_kt<1, 4, T>(tv, kp, data, ld, nchan, ov, st);
+  if (tv.ntiles * ((nchan + 63) / 64) <= 256) launch_kt<1, 8, T>(tv, kp, data, ld, nchan, ov, st);
+  else if (nchan <= 64 || few) launch_kt<1, 4, T>(tv, kp, data, ld, nchan, ov, st);
   else if (nchan <= 128) launch_kt<2, 2, T>(tv, kp, data, ld, nchan, ov, st);
   else launch_kt<4, 1, T>(tv, kp, data, ld, nchan, ov, st);
 }
