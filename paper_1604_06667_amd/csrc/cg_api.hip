@@ -157,10 +157,9 @@ cg_status run_lookup(cg_gridder* g, const double* lon, const double* lat, int64_
          "radix sort");
   g->sorted_keys = in_tmp ? w.keys2 : w.keys;
   g->sorted_vals = in_tmp ? w.vals2 : w.vals;
-  CG_HIP(cg::launch_ring_offsets(g->sorted_keys, n, nside, w.ring_off, st), "ring offsets");
-  CG_HIP(cg::launch_permute(g->sorted_vals, w.ring_off + 4 * nside, n, w.rec, data, dtype, ld,
-                            g->nchan, with_data, npack, w.srec, w.sdata, st),
-         "permute");
+  CG_HIP(cg::launch_permute(g->sorted_keys, g->sorted_vals, n, nside, w.ring_off, w.rec, data, dtype,
+                            ld, g->nchan, with_data, npack, w.srec, w.sdata, st),
+         "ring offsets, permute");
   g->last_n = n;
   g->have_ranges = false;
   if (g->lookup == CG_LOOKUP_DISK) {

@@ -168,11 +168,13 @@ struct RangeWindow {
 // resident together in that XCD's L2; what is left after the last full round
 // is split evenly.  A quarter of an XCD's tiles per run keeps a run large
 // against the tiles resident at once on big maps, and spreads the work where
-// the samples cover only a part of the map (a scan of an eighth of a 301 x
-// 257 map, 320 tiles: 0.36 ms with one run per XCD, as all of them fell to
-// one or two XCDs).
+// the samples cover only a part of the map; small maps take sixteen runs, so
+// that a part of them is spread too (eight scans of an eighth of a 301 x 257
+// map each: 4.3 ms with one run per XCD, 2.40 with four, 2.25 with sixteen; a
+// 600 x 600 cube loses 4 % with sixteen against four).
 __device__ __forceinline__ int64_t tile_of_block(int64_t b, int64_t ntiles, int64_t npass = 1) {
-  const int64_t run = npass * (1 + ntiles / (npass * kNumXcd * 4));
+  const int64_t tiles = ntiles / npass;
+  const int64_t run = npass * (1 + tiles / (kNumXcd * (tiles <= 2048 ? 16 : 4)));
   const int64_t round = kNumXcd * run;
   const int64_t k = b % kNumXcd;
   const int64_t j = b / kNumXcd;
@@ -362,15 +364,16 @@ hipError_t radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32
                       uint32_t* hist, int64_t n, int bits, bool iota, bool* result_in_tmp,
                       hipStream_t st);
 size_t radix_hist_elems(int64_t n);   // histogram and digit totals
-hipError_t launch_ring_offsets(const uint32_t* keys, int64_t n, int64_t nside, uint32_t* ring_off,
-                               hipStream_t st);
+// ring offsets and the permutation of the sorted samples:
 // srec: one record per sorted sample (unit vector; input row as int64 bits, or
 // with data and npack > 0 the channels 0-1 as FP32); sdata: the rows of narrow
 // FP32 grids of more channels
-hipError_t launch_permute(const uint32_t* vals, const uint32_t* nvalid_dev, int64_t n,
-                          const double* rec, const void* data, int dtype, int64_t ld,
-                          int64_t nchan, bool with_data, int npack, double* srec,
+hipError_t launch_permute(const uint32_t* keys, const uint32_t* vals, int64_t n, int64_t nside,
+                          uint32_t* ring_off, const double* rec, const void* data, int dtype,
+                          int64_t ld, int64_t nchan, bool with_data, int npack, double* srec,
                           float* sdata, hipStream_t st);
+hipError_t launch_ring_offsets(const uint32_t* keys, int64_t n, int64_t nside, uint32_t* ring_off,
+                               hipStream_t st);
 hipError_t scan_u64(const uint64_t* in, uint64_t* out, int64_t n, hipStream_t st);
 // the same over many blocks; scratch holds scan_u64_wide_scratch(n) values
 size_t scan_u64_wide_scratch(int64_t n);

@@ -626,9 +626,8 @@ hipError_t launch_batch_permute(const BatchJob* jobs, const int64_t* noff, int n
 // ring_off[i] = first sorted position whose key is >= ring_start(i), for
 // i = 1 .. 4 nside; ring_off[4 nside] is the number of valid samples.
 
-__global__ void __launch_bounds__(256) k_ring_offsets(const uint32_t* __restrict__ keys, int64_t n,
-                                                      int64_t nside, uint32_t* __restrict__ ring_off) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x + 1;
+__device__ __forceinline__ void ring_offset(const uint32_t* __restrict__ keys, int64_t n, int64_t nside,
+                                            int64_t i, uint32_t* __restrict__ ring_off) {
   if (i > 4 * nside) return;
   const uint64_t target = (uint64_t)hpx::ring_start(nside, i);
   int64_t lo = 0, hi = n;
@@ -639,6 +638,11 @@ __global__ void __launch_bounds__(256) k_ring_offsets(const uint32_t* __restrict
   }
   ring_off[i] = (uint32_t)lo;
   if (i == 1) ring_off[0] = 0;
+}
+
+__global__ void __launch_bounds__(256) k_ring_offsets(const uint32_t* __restrict__ keys, int64_t n,
+                                                      int64_t nside, uint32_t* __restrict__ ring_off) {
+  ring_offset(keys, n, nside, (int64_t)blockIdx.x * blockDim.x + threadIdx.x + 1, ring_off);
 }
 
 hipError_t launch_ring_offsets(const uint32_t* keys, int64_t n, int64_t nside, uint32_t* ring_off,
@@ -658,17 +662,33 @@ hipError_t launch_ring_offsets(const uint32_t* keys, int64_t n, int64_t nside, u
 // stored behind their unit vectors, one stretch per sample, cost more here
 // than the gather gained: 12 million x 8 channels 0.77 -> 0.91 ms.
 
-template <typename T, bool VEC4>
-__global__ void __launch_bounds__(256) k_permute(const uint32_t* __restrict__ vals,
-                                                 const uint32_t* __restrict__ nvalid_p,
+//
+// RINGS: the first nrb blocks find the ring offsets, and the permutation tells
+// the valid samples by their keys, so that up to kRingMerge samples need one
+// launch for both (a map of 20,000 samples: the call 64.1 -> 61.4 us); beyond, the keys'
+// bytes cost more than the launch.
+constexpr int64_t kRingMerge = 1 << 20;
+
+template <typename T, bool VEC4, bool RINGS>
+__global__ void __launch_bounds__(256) k_permute(const uint32_t* __restrict__ keys,
+                                                 const uint32_t* __restrict__ vals, int64_t n,
+                                                 int64_t nside, int nrb, uint32_t* ring_off,
                                                  const double4* __restrict__ rec,
                                                  const T* __restrict__ data, int64_t ld,
                                                  int64_t nchan, int with_data, int npack,
                                                  double4* __restrict__ srec,
                                                  float* __restrict__ sdata) {
-  const int64_t nvalid = (int64_t)(*nvalid_p);
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= nvalid) return;
+  int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if constexpr (RINGS) {
+    if ((int)blockIdx.x < nrb) {
+      ring_offset(keys, n, nside, p + 1, ring_off);
+      return;
+    }
+    p -= (int64_t)nrb * blockDim.x;
+    if (p >= n || keys[p] >= (uint32_t)hpx::npix(nside)) return;
+  } else {
+    if (p >= (int64_t)ring_off[4 * nside]) return;
+  }
   const int64_t src = vals[p];
   const double4 r = rec[src];
   if (with_data && npack > 0) {
@@ -689,39 +709,41 @@ __global__ void __launch_bounds__(256) k_permute(const uint32_t* __restrict__ va
   }
 }
 
-hipError_t launch_permute(const uint32_t* vals, const uint32_t* nvalid_dev, int64_t n,
-                          const double* rec, const void* data, int dtype, int64_t ld,
-                          int64_t nchan, bool with_data, int npack, double* srec,
+hipError_t launch_permute(const uint32_t* keys, const uint32_t* vals, int64_t n, int64_t nside,
+                          uint32_t* ring_off, const double* rec, const void* data, int dtype,
+                          int64_t ld, int64_t nchan, bool with_data, int npack, double* srec,
                           float* sdata, hipStream_t st) {
-  // nvalid_dev points at the number of valid samples (ring_off[4 nside]);
-  // the grid covers all n sorted entries and threads past it return.
   if (n <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((n + 255) / 256)), blk(256);
+  const bool rings = n <= kRingMerge;
+  const int nrb = rings ? (int)((4 * nside + 255) / 256) : 0;
+  if (!rings) {
+    const hipError_t e = launch_ring_offsets(keys, n, nside, ring_off, st);
+    if (e != hipSuccess) return e;
+  }
+  // the grid covers all n sorted entries; threads of invalid ones return
+  const dim3 grid((unsigned)((n + 255) / 256 + nrb)), blk(256);
   const int wd = with_data ? 1 : 0;
   const double4* r = reinterpret_cast<const double4*>(rec);
   double4* sr = reinterpret_cast<double4*>(srec);
+#define CG_PERMUTE(T, VEC4)                                                                        \
+  do {                                                                                             \
+    if (rings)                                                                                     \
+      hipLaunchKernelGGL((k_permute<T, VEC4, true>), grid, blk, 0, st, keys, vals, n, nside, nrb,  \
+                         ring_off, r, (const T*)data, ld, nchan, wd, npack, sr, sdata);            \
+    else                                                                                           \
+      hipLaunchKernelGGL((k_permute<T, VEC4, false>), grid, blk, 0, st, keys, vals, n, nside, nrb, \
+                         ring_off, r, (const T*)data, ld, nchan, wd, npack, sr, sdata);            \
+  } while (0)
   switch (dtype) {
-    case 0:
-      hipLaunchKernelGGL((k_permute<double, false>), grid, blk, 0, st, vals, nvalid_dev, r,
-                         (const double*)data, ld, nchan, wd, npack, sr, sdata);
-      break;
+    case 0: CG_PERMUTE(double, false); break;
     case 1:
-      if (wd && nchan % 4 == 0 && ld % 4 == 0 && ((uintptr_t)data & 15) == 0)
-        hipLaunchKernelGGL((k_permute<float, true>), grid, blk, 0, st, vals, nvalid_dev, r,
-                           (const float*)data, ld, nchan, wd, npack, sr, sdata);
-      else
-        hipLaunchKernelGGL((k_permute<float, false>), grid, blk, 0, st, vals, nvalid_dev, r,
-                           (const float*)data, ld, nchan, wd, npack, sr, sdata);
+      if (wd && nchan % 4 == 0 && ld % 4 == 0 && ((uintptr_t)data & 15) == 0) CG_PERMUTE(float, true);
+      else CG_PERMUTE(float, false);
       break;
-    case 2:
-      hipLaunchKernelGGL((k_permute<_Float16, false>), grid, blk, 0, st, vals, nvalid_dev, r,
-                         (const _Float16*)data, ld, nchan, wd, npack, sr, sdata);
-      break;
-    default:
-      hipLaunchKernelGGL((k_permute<uint16_t, false>), grid, blk, 0, st, vals, nvalid_dev, r,
-                         (const uint16_t*)data, ld, nchan, wd, npack, sr, sdata);
-      break;
+    case 2: CG_PERMUTE(_Float16, false); break;
+    default: CG_PERMUTE(uint16_t, false); break;
   }
+#undef CG_PERMUTE
   return hipGetLastError();
 }
 
