@@ -12,8 +12,8 @@
 // without a tail of idle compute units.
 // Each item runs the same tile contraction as the per-grid kernel, with the
 // kernel type (circular or elliptical) taken from the job at run time where
-// the batch holds both, and
-// writes the normalised cube and weights of its job directly.
+// the batch holds both, and writes the normalised cube and weights of its job
+// directly.
 #include "cg_internal.hpp"
 
 namespace cg {

@@ -5,10 +5,10 @@
 
 namespace cg {
 
+// One block of accumulators per wavefront leaves room for four wavefronts on a
+// SIMD: without the bound some data types took a few registers too many, and
+// 11.8 ms became 15.7 on the sight lines in FP16.
 template <int NW, int BPW, int KT, bool SHORT, int MODE, bool FULL, typename T, int KS>
-// (one block of accumulators per wavefront leaves room for four wavefronts on
-// a SIMD: without the bound some data types took a few registers too many,
-// and 11.8 ms became 15.7 on the sight lines in FP16)
 __global__ void __launch_bounds__(NW * 64, BPW == 1 ? 4 : 1) k_gather_mfma(TileView tv, KernelParams kp,
                                                          const T* __restrict__ data,
                                                          const T* __restrict__ zrow, int64_t ld,
