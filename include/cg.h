@@ -400,9 +400,9 @@ cg_status cg_batch_tune(cg_batch* b, const cg_batch_job* in, int32_t reps, void*
 /* Record one cg_batch_grid step on `in` as a HIP graph (after running it
  * once eagerly to size every buffer), for replay by cg_batch_replay without
  * host synchronisation.  The graph keeps the device pointers and sample
- * counts of `in`: a replay grids whatever those buffers hold when it runs.
- * A later cg_batch_grid that must enlarge a buffer, or cg_batch_tune, drops
- * the graph.  Waits for the device.  Errors as cg_batch_grid. */
+ * counts of `in`: a replay grids whatever those buffers hold when it runs,
+ * whatever other inputs passes have gridded since.  A later cg_batch_grid
+ * that must enlarge a buffer, or cg_batch_tune, drops the graph.  Waits for the device.  Errors as cg_batch_grid. */
 cg_status cg_batch_capture(cg_batch* b, const cg_batch_job* in, void* stream);
 
 /* Launch the captured graph on `stream`.  Errors: CG_E_STATE (no graph),

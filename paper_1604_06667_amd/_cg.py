@@ -515,6 +515,7 @@ class Batch:
         check(lib().cg_batch_create(C.byref(h), arr, len(self.gridders), codes[dtype]))
         self._h = h
         self._keep = None
+        self._graph_keep = None   # what a captured graph points to
 
     def __del__(self):
         try:
@@ -560,16 +561,18 @@ class Batch:
         arr, keep = self._jobs(inputs, outputs)
         check(lib().cg_batch_grid(self._h, arr, _stream(stream)))
         self._keep = keep
+        if self._graph_keep is not None and not self.query(8):
+            self._graph_keep = None
 
     def tune(self, inputs, outputs, reps=3, stream=None):
         arr, keep = self._jobs(inputs, outputs)
         check(lib().cg_batch_tune(self._h, arr, int(reps), _stream(stream)))
-        self._keep = keep
+        self._keep, self._graph_keep = keep, None
 
     def capture(self, inputs, outputs, stream=None):
         arr, keep = self._jobs(inputs, outputs)
         check(lib().cg_batch_capture(self._h, arr, _stream(stream)))
-        self._keep = keep   # the graph holds these pointers
+        self._keep = self._graph_keep = keep   # the graph holds these pointers
 
     def replay(self, stream=None):
         check(lib().cg_batch_replay(self._h, _stream(stream)))

@@ -22,12 +22,11 @@ struct cg_batch {
   std::vector<int64_t> noff;                 // sample offsets, size njobs + 1
   int64_t ntot = 0;
   std::vector<cg::BatchJob> hjobs;           // host copy of the job table
-  cg::BatchJob* pin_jobs = nullptr;          // pinned staging of the job table
+  cg::BatchJob* pin_jobs = nullptr;          // pinned staging of the job table, then of the captured one
   int64_t* pin_off = nullptr;                // pinned staging of noff | toff | rooff
   uint64_t* pin_word = nullptr;
   DevBuf d_jobs, d_off, keys, vals, keys2, vals2, hist, ring_off, sx, ranges, nranges, ncand,
       zrow, items, counter, flags;
-  bool sorted_in_tmp = false;               // which key/value buffers hold the sorted run
   // work queue
   std::vector<cg::BatchItem> hitems;
   cg::BatchItem* pin_items = nullptr;
@@ -41,9 +40,14 @@ struct cg_batch {
   // the tuner's choice on all of four batches of 6 to 16 jobs; the largest
   // takes 3.0 ms so, 3.4 with eight wavefronts of one block and 3.5 of two)
   int shape = 3, split = 0, bpc = 0;
-  // kernel form of the uploaded job table, and of the captured graph
-  int form = cg::BATCH_ANY, graph_form = cg::BATCH_ANY;
-  // graph
+  int form = cg::BATCH_ANY;                  // kernel form of the uploaded job table
+  // graph: the pass over cap_in, with a job table and offsets of its own that
+  // later passes on other inputs leave alone
+  std::vector<cg_batch_job> cap_in;
+  std::vector<cg::BatchJob> cap_hjobs;
+  std::vector<int64_t> cap_noff;
+  DevBuf cap_jobs, cap_off;
+  int graph_form = cg::BATCH_ANY;
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -192,29 +196,19 @@ int form_of(const cg_batch* b) {
   return form;
 }
 
-// Job table and offsets for the inputs `in`; uploads them on `st`.
-cg_status upload_tables(cg_batch* b, const cg_batch_job* in, hipStream_t st) {
+// Job table of a pass over `in`, whose sample offsets are noff.
+cg_status fill_jobs(const cg_batch* b, const cg_batch_job* in, const std::vector<int64_t>& noff,
+                    std::vector<cg::BatchJob>* table) {
   const int njobs = (int)b->jobs.size();
-  for (int j = 0; j < njobs; ++j) {
-    // the batch's offsets were laid out for each gridder's kernel and nside
-    const cg_gridder* g = b->jobs[j];
-    if (!g->span_valid || g->nside != b->snap_nside[(size_t)j] ||
-        g->total_ranges != b->snap_ranges[(size_t)j])
-      return fail(CG_E_STATE, "job %d: gridder kernel or nside changed since cg_batch_create", j);
-  }
-  b->noff.assign((size_t)njobs + 1, 0);
-  for (int j = 0; j < njobs; ++j) b->noff[(size_t)j + 1] = b->noff[(size_t)j] + in[j].nsamples;
-  b->ntot = b->noff[(size_t)njobs];
-  if (b->ntot > 0xFFFFFFFFll - 1) return fail(CG_E_UNSUPPORTED, "batch has >= 2^32 samples");
-  b->hjobs.resize((size_t)njobs);
+  table->resize((size_t)njobs);
   for (int j = 0; j < njobs; ++j) {
     const cg_gridder* g = b->jobs[j];
-    cg::BatchJob& q = b->hjobs[(size_t)j];
+    cg::BatchJob& q = (*table)[(size_t)j];
     q.lon = in[j].lon_deg;
     q.lat = in[j].lat_deg;
     q.data = in[j].data;
     q.n = in[j].nsamples;
-    q.noff = b->noff[(size_t)j];
+    q.noff = noff[(size_t)j];
     q.ld = in[j].ld_data;
     q.nchan = g->nchan;
     q.nside = g->nside;
@@ -240,6 +234,25 @@ cg_status upload_tables(cg_batch* b, const cg_batch_job* in, hipStream_t st) {
     q.kp = g->kp;
     q.rho = g->support_rad + 1e-9;
   }
+  return CG_OK;
+}
+
+// Job table and offsets for the inputs `in`; uploads them on `st`.
+cg_status upload_tables(cg_batch* b, const cg_batch_job* in, hipStream_t st) {
+  const int njobs = (int)b->jobs.size();
+  for (int j = 0; j < njobs; ++j) {
+    // the batch's offsets were laid out for each gridder's kernel and nside
+    const cg_gridder* g = b->jobs[j];
+    if (!g->span_valid || g->nside != b->snap_nside[(size_t)j] ||
+        g->total_ranges != b->snap_ranges[(size_t)j])
+      return fail(CG_E_STATE, "job %d: gridder kernel or nside changed since cg_batch_create", j);
+  }
+  b->noff.assign((size_t)njobs + 1, 0);
+  for (int j = 0; j < njobs; ++j) b->noff[(size_t)j + 1] = b->noff[(size_t)j] + in[j].nsamples;
+  b->ntot = b->noff[(size_t)njobs];
+  if (b->ntot > 0xFFFFFFFFll - 1) return fail(CG_E_UNSUPPORTED, "batch has >= 2^32 samples");
+  cg_status s = fill_jobs(b, in, b->noff, &b->hjobs);
+  if (s != CG_OK) return s;
   b->form = form_of(b);
   // staging buffers are reused: the previous upload must be complete
   CG_HIP(hipStreamSynchronize(st), "sync tables");
@@ -259,49 +272,54 @@ cg_status upload_tables(cg_batch* b, const cg_batch_job* in, hipStream_t st) {
   return CG_OK;
 }
 
-const int64_t* dev_noff(const cg_batch* b) { return b->d_off.as<int64_t>(); }
-const int64_t* dev_toff(const cg_batch* b) { return b->d_off.as<int64_t>() + b->jobs.size() + 1; }
-const int64_t* dev_rooff(const cg_batch* b) {
-  return b->d_off.as<int64_t>() + 2 * (b->jobs.size() + 1);
+// What the device work of a pass runs on: the job table and its offsets
+// (samples, tiles, ring offsets), and what the launches take from them.
+struct PassTables {
+  const cg::BatchJob* jobs;
+  const int64_t* off;
+  int64_t ntot;
+  int form;
+};
+
+PassTables pass_tables(const cg_batch* b) {
+  return {b->d_jobs.as<cg::BatchJob>(), b->d_off.as<int64_t>(), b->ntot, b->form};
+}
+PassTables captured_tables(const cg_batch* b) {
+  return {b->cap_jobs.as<cg::BatchJob>(), b->cap_off.as<int64_t>(), b->cap_noff.back(),
+          b->graph_form};
 }
 
 // Device work of one pass up to the candidate scan (no host synchronisation).
-cg_status lookup_part(cg_batch* b, hipStream_t st) {
+cg_status lookup_part(cg_batch* b, const PassTables& p, hipStream_t st) {
   const int njobs = (int)b->jobs.size();
-  const cg::BatchJob* dj = b->d_jobs.as<cg::BatchJob>();
+  const int64_t *noff = p.off, *toff = noff + njobs + 1, *rooff = toff + njobs + 1;
   int* flags = b->flags.as<int>();
-  CG_HIP(cg::launch_batch_prep(dj, dev_noff(b), njobs, b->ntot, b->keys.as<uint32_t>(),
+  CG_HIP(cg::launch_batch_prep(p.jobs, noff, njobs, p.ntot, b->keys.as<uint32_t>(),
                                b->vals.as<uint32_t>(), flags, st),
          "batch prep");
   bool in_tmp = false;
   CG_HIP(cg::radix_sort_jobs(b->keys.as<uint32_t>(), b->vals.as<uint32_t>(),
                              b->keys2.as<uint32_t>(), b->vals2.as<uint32_t>(),
-                             b->hist.as<uint32_t>(), b->ntot, b->bits, false, dev_noff(b), njobs,
+                             b->hist.as<uint32_t>(), p.ntot, b->bits, false, noff, njobs,
                              &in_tmp, st),
          "batch sort");
-  b->sorted_in_tmp = in_tmp;
   const uint32_t* skeys = in_tmp ? b->keys2.as<uint32_t>() : b->keys.as<uint32_t>();
   const uint32_t* svals = in_tmp ? b->vals2.as<uint32_t>() : b->vals.as<uint32_t>();
-  CG_HIP(cg::launch_batch_ring_offsets(dj, dev_rooff(b), njobs, b->nro, skeys,
+  CG_HIP(cg::launch_batch_ring_offsets(p.jobs, rooff, njobs, b->nro, skeys,
                                        b->ring_off.as<uint32_t>(), st),
          "batch ring offsets");
-  CG_HIP(cg::launch_batch_permute(dj, dev_noff(b), njobs, b->ntot, svals,
+  CG_HIP(cg::launch_batch_permute(p.jobs, noff, njobs, p.ntot, svals,
                                   b->ring_off.as<uint32_t>(), b->sx.as<double>(), st),
          "batch permute");
-  CG_HIP(cg::launch_batch_tile_ranges(dj, dev_toff(b), njobs, b->ntiles, skeys,
+  CG_HIP(cg::launch_batch_tile_ranges(p.jobs, toff, njobs, b->ntiles, skeys,
                                       b->ring_off.as<uint32_t>(), b->ranges.as<uint32_t>(),
                                       b->nranges.as<uint32_t>(), b->ncand.as<uint64_t>(), st),
          "batch tile ranges");
   return CG_OK;
 }
 
-const uint32_t* sorted_vals(const cg_batch* b) {
-  return b->sorted_in_tmp ? b->vals2.as<uint32_t>() : b->vals.as<uint32_t>();
-}
-
 // Device work after the lookup: the persistent contraction over the queue.
-cg_status contract_part(cg_batch* b, hipStream_t st, bool events) {
-  const cg::BatchJob* dj = b->d_jobs.as<cg::BatchJob>();
+cg_status contract_part(cg_batch* b, const PassTables& p, hipStream_t st, bool events) {
   CG_HIP(cg::launch_fill(b->counter.as<float>(), cg::kNumXcd, 0.0f, st), "clear counters");
   std::pair<hipEvent_t, hipEvent_t>* pe = nullptr;
   if (events) {
@@ -314,8 +332,8 @@ cg_status contract_part(cg_batch* b, hipStream_t st, bool events) {
   br.nranges = b->nranges.as<uint32_t>();
   br.ncand = b->ncand.as<uint64_t>();
   br.srec = reinterpret_cast<const double4*>(b->sx.as<double>());
-  CG_HIP(cg::launch_batch_mfma(dj, b->items.as<cg::BatchItem>(), b->queues, b->counter.as<int>(),
-                               br, b->zrow.p, b->dtype, b->prec, b->shape, b->form, b->bpc, st),
+  CG_HIP(cg::launch_batch_mfma(p.jobs, b->items.as<cg::BatchItem>(), b->queues, b->counter.as<int>(),
+                               br, b->zrow.p, b->dtype, b->prec, b->shape, p.form, b->bpc, st),
          "batch contraction");
   if (pe) CG_HIP(hipEventRecord(pe->second, st), "event record");
   return CG_OK;
@@ -343,6 +361,53 @@ bool need_items(const cg_batch* b, const cg_batch_job* in) {
   return false;
 }
 
+// Records the device work of a pass over the captured tables as the graph
+// (every buffer has its size by now).
+cg_status record_graph(cg_batch* b) {
+  drop_graph(b);
+  hipStream_t cs = b->cap_stream;
+  CG_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal), "begin capture");
+  const PassTables p = captured_tables(b);
+  cg_status s = lookup_part(b, p, cs);
+  if (s == CG_OK) s = contract_part(b, p, cs, false);
+  hipGraph_t graph = nullptr;
+  hipError_t e = hipStreamEndCapture(cs, &graph);
+  if (s != CG_OK) {
+    if (graph) (void)hipGraphDestroy(graph);
+    return s;
+  }
+  if (e != hipSuccess) return hip_fail(e, "end capture");
+  hipGraphExec_t exec = nullptr;
+  e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+  if (e != hipSuccess) {
+    (void)hipGraphDestroy(graph);
+    return hip_fail(e, "instantiate graph");
+  }
+  b->graph = graph;
+  b->exec = exec;
+  return CG_OK;
+}
+
+// A pass takes the gridders as they are now; so do the replays after it: the
+// captured job table follows a kernel or layout set since, and the graph is
+// recorded again where its contraction does not cover the new kernels.
+cg_status follow_gridders(cg_batch* b, hipStream_t st) {
+  std::vector<cg::BatchJob> now;
+  cg_status s = fill_jobs(b, b->cap_in.data(), b->cap_noff, &now);
+  if (s != CG_OK) return s;
+  const size_t bytes = sizeof(cg::BatchJob) * now.size();
+  if (memcmp(now.data(), b->cap_hjobs.data(), bytes) != 0) {
+    b->cap_hjobs = now;
+    cg::BatchJob* pin = b->pin_jobs + now.size();   // (upload_tables has waited for `st`)
+    memcpy(pin, now.data(), bytes);
+    CG_HIP(hipMemcpyAsync(b->cap_jobs.p, pin, bytes, hipMemcpyHostToDevice, st),
+           "upload captured jobs");
+  }
+  if (b->form <= b->graph_form) return CG_OK;
+  b->graph_form = b->form;
+  return record_graph(b);
+}
+
 // One eager pass: tables, lookup and contraction.  Every buffer is sized
 // from the sample counts (known on the host), so the pass does not wait for
 // the device except to reuse the pinned staging buffers of the tables.
@@ -351,8 +416,10 @@ cg_status eager_pass(cg_batch* b, const cg_batch_job* in, hipStream_t st) {
   if (s != CG_OK) return s;
   if ((s = size_pass(b)) != CG_OK) return s;
   if (need_items(b, in) && (s = build_items(b, in, st)) != CG_OK) return s;
-  if ((s = lookup_part(b, st)) != CG_OK) return s;
-  return contract_part(b, st, true);
+  if (b->exec && (s = follow_gridders(b, st)) != CG_OK) return s;
+  const PassTables p = pass_tables(b);
+  if ((s = lookup_part(b, p, st)) != CG_OK) return s;
+  return contract_part(b, p, st, true);
 }
 
 }  // namespace
@@ -415,6 +482,8 @@ cg_status cg_batch_create(cg_batch** out, cg_gridder* const* jobs, int32_t njobs
   const Allocator& al = b->alloc;
   if ((e = ensure(al, b->d_jobs, sizeof(cg::BatchJob) * njobs)) != hipSuccess ||
       (e = ensure(al, b->d_off, sizeof(int64_t) * 3 * (njobs + 1))) != hipSuccess ||
+      (e = ensure(al, b->cap_jobs, sizeof(cg::BatchJob) * njobs)) != hipSuccess ||
+      (e = ensure(al, b->cap_off, sizeof(int64_t) * 3 * (njobs + 1))) != hipSuccess ||
       (e = ensure(al, b->ring_off, 4 * std::max<int64_t>(b->nro, 1))) != hipSuccess ||
       (e = ensure(al, b->ranges, 8 * std::max<int64_t>(b->nranges_tot, 1))) != hipSuccess ||
       (e = ensure(al, b->nranges, 4 * nt)) != hipSuccess ||
@@ -425,7 +494,7 @@ cg_status cg_batch_create(cg_batch** out, cg_gridder* const* jobs, int32_t njobs
   if ((e = hipMemset(b->zrow.p, 0, 8 * 512)) != hipSuccess ||
       (e = hipMemset(b->flags.p, 0, 64)) != hipSuccess)
     return done(hip_fail(e, "clear batch"));
-  if ((e = hipHostMalloc((void**)&b->pin_jobs, sizeof(cg::BatchJob) * njobs,
+  if ((e = hipHostMalloc((void**)&b->pin_jobs, sizeof(cg::BatchJob) * 2 * njobs,
                          hipHostMallocDefault)) != hipSuccess ||
       (e = hipHostMalloc((void**)&b->pin_off, sizeof(int64_t) * 3 * (njobs + 1),
                          hipHostMallocDefault)) != hipSuccess ||
@@ -470,12 +539,12 @@ cg_status cg_batch_tune(cg_batch* b, const cg_batch_job* in, int32_t reps, void*
         b->bpc = bpc;
         if ((s = build_items(b, in, st)) != CG_OK) break;
         // one untimed run, then reps timed
-        if ((s = contract_part(b, st, false)) != CG_OK) break;
+        if ((s = contract_part(b, pass_tables(b), st, false)) != CG_OK) break;
         if (hipEventRecord(e0, st) != hipSuccess) {
           s = fail(CG_E_DEVICE, "event");
           break;
         }
-        for (int r = 0; r < reps && s == CG_OK; ++r) s = contract_part(b, st, false);
+        for (int r = 0; r < reps && s == CG_OK; ++r) s = contract_part(b, pass_tables(b), st, false);
         if (s != CG_OK) break;
         if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
           s = fail(CG_E_DEVICE, "event");
@@ -503,7 +572,7 @@ cg_status cg_batch_tune(cg_batch* b, const cg_batch_job* in, int32_t reps, void*
   if (s != CG_OK) return s;
   if ((s = build_items(b, in, st)) != CG_OK) return s;
   // leave the outputs from the chosen shape
-  if ((s = contract_part(b, st, false)) != CG_OK) return s;
+  if ((s = contract_part(b, pass_tables(b), st, false)) != CG_OK) return s;
   CG_HIP(hipStreamSynchronize(st), "sync tune");
   return CG_OK;
 }
@@ -515,29 +584,20 @@ cg_status cg_batch_capture(cg_batch* b, const cg_batch_job* in, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   drop_graph(b);
   if ((s = eager_pass(b, in, st)) != CG_OK) return s;
+  // the pass's own tables, for the graph alone
+  const size_t njobs = b->jobs.size();
+  CG_HIP(hipMemcpyAsync(b->cap_jobs.p, b->d_jobs.p, sizeof(cg::BatchJob) * njobs,
+                        hipMemcpyDeviceToDevice, st),
+         "copy jobs");
+  CG_HIP(hipMemcpyAsync(b->cap_off.p, b->d_off.p, sizeof(int64_t) * 3 * (njobs + 1),
+                        hipMemcpyDeviceToDevice, st),
+         "copy offsets");
   CG_HIP(hipStreamSynchronize(st), "sync before capture");
-  // every buffer is sized for `in`; record the device work of one pass
-  hipStream_t cs = b->cap_stream;
-  CG_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal), "begin capture");
-  cg_status s1 = lookup_part(b, cs);
-  if (s1 == CG_OK) s1 = contract_part(b, cs, false);
-  hipGraph_t graph = nullptr;
-  hipError_t e = hipStreamEndCapture(cs, &graph);
-  if (s1 != CG_OK) {
-    if (graph) (void)hipGraphDestroy(graph);
-    return s1;
-  }
-  if (e != hipSuccess) return hip_fail(e, "end capture");
-  hipGraphExec_t exec = nullptr;
-  e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-  if (e != hipSuccess) {
-    (void)hipGraphDestroy(graph);
-    return hip_fail(e, "instantiate graph");
-  }
-  b->graph = graph;
-  b->exec = exec;
+  b->cap_in.assign(in, in + njobs);
+  b->cap_hjobs = b->hjobs;
+  b->cap_noff = b->noff;
   b->graph_form = b->form;
-  return CG_OK;
+  return record_graph(b);
 }
 
 cg_status cg_batch_replay(cg_batch* b, void* stream) {
@@ -556,14 +616,8 @@ cg_status cg_batch_replay(cg_batch* b, void* stream) {
   cg_status s = batch_event(b, &pe);
   if (s != CG_OK) return s;
   if (pe) CG_HIP(hipEventRecord(pe->first, st), "event record");
-  if (b->form > b->graph_form) {
-    // a pass since the capture has uploaded kernels that the graph's
-    // contraction does not cover: the same work, launched one by one
-    if ((s = lookup_part(b, st)) != CG_OK) return s;
-    if ((s = contract_part(b, st, false)) != CG_OK) return s;
-  } else {
-    CG_HIP(hipGraphLaunch(b->exec, st), "graph launch");
-  }
+  b->ntot = b->cap_noff.back();
+  CG_HIP(hipGraphLaunch(b->exec, st), "graph launch");
   if (pe) CG_HIP(hipEventRecord(pe->second, st), "event record");
   return CG_OK;
 }
@@ -643,7 +697,7 @@ void cg_batch_destroy(cg_batch* b) {
     (void)hipEventDestroy(e.first);
     (void)hipEventDestroy(e.second);
   }
-  DevBuf* bufs[] = {&b->d_jobs, &b->d_off, &b->keys, &b->vals, &b->keys2, &b->vals2, &b->hist,
+  DevBuf* bufs[] = {&b->d_jobs, &b->d_off, &b->cap_jobs, &b->cap_off, &b->keys, &b->vals, &b->keys2, &b->vals2, &b->hist,
                     &b->ring_off, &b->sx, &b->ranges, &b->nranges, &b->ncand, &b->zrow,
                     &b->items, &b->counter, &b->flags};
   for (DevBuf* d : bufs) d->release();
