@@ -437,13 +437,20 @@ __global__ void __launch_bounds__(kSortThreads) k_scatter(
 // us with 4 against 82 with 16; a million: 75 with 8, 85 with 16); many beyond,
 // for long runs of a digit in the writes (47.2 million of 26 bits: 1196 us with
 // 16 and 512 threads, 1439 with 256 threads, 3323 with 4).
+constexpr int64_t kSortBlocks = 256;
 static int sort_items(int64_t n) {
-  return n <= 256 * 4 * kSortThreads ? 4 : n <= 256 * 8 * kSortThreads ? 8 : 16;
+  return n <= kSortBlocks * 4 * kSortThreads ? 4 : n <= kSortBlocks * 8 * kSortThreads ? 8 : 16;
 }
 
+// For n pairs or fewer: a sort of fewer pairs may have more blocks, but with
+// less than 16 pairs per thread never more than kSortBlocks, nor more than n
+// pairs make with 4.
 size_t radix_hist_elems(int64_t n) {
-  const int64_t tile = (int64_t)kSortThreads * sort_items(n);
-  const int64_t nb = (n + tile - 1) / tile;
+  const int64_t tile = (int64_t)kSortThreads * sort_items(n), least = 4 * (int64_t)kSortThreads;
+  int64_t nb = (n + tile - 1) / tile;
+  int64_t below = (n + least - 1) / least;
+  if (below > kSortBlocks) below = kSortBlocks;
+  if (nb < below) nb = below;
   return ((size_t)(nb < 1 ? 1 : nb) + 1) << kDigitBits;
 }
 

@@ -92,3 +92,25 @@ def test_captured_buffers_stay_alive():
     b.tune(other, b.outputs(), reps=1)   # drops the graph
     gc.collect()
     assert all(r() is None for r in refs)
+
+
+def test_graph_survives_passes_of_fewer_samples():
+    """Pair counts on both sides of the sizes where the sort's blocks double."""
+    import dataclasses
+
+    import numpy as np
+    import torch
+    import paper_1604_06667_amd as cgp
+    from gpu_util import make_gridder, to_device
+    from test_gpu_gather_wide import _field
+    wl = _field(33, 17, 1_200_000, 17)
+    g = make_gridder(wl, "bf16")
+    lon, lat, d = to_device(wl)
+    b = cgp.Batch([g], torch.float32)
+    for n, fewer in ((600_000, (524_288, 500_000)), (1_150_000, (1_048_576, 1_000_000, 500_000))):
+        ins, outs = [(lon[:n], lat[:n], d[:n])], b.outputs()
+        b.capture(ins, outs)
+        for m in fewer:
+            b.grid([(lon[:m], lat[:m], d[:m])], b.outputs())
+            assert b.query(8) == 1, (n, m)
+        _check(b, [g], ins, outs, times=1)
