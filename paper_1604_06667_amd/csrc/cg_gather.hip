@@ -35,7 +35,9 @@ typedef float f32x16_t __attribute__((ext_vector_type(16)));
 // v_mfma_f32_32x32x2 per 32 x 32 pairs, whose sign bits are shifted into the
 // masks, one vector instruction per pair and lane.  The FP32 values are
 // widened by 4e-6 of the squared extent of the tile and its support (64
-// roundings), so the marks are a superset and the FP64 test alone decides.
+// roundings), and the support by 2e-15 for the rounding of u and v in FP64
+// (products of unit vectors: 3e-16 each, which counts for supports below
+// 1e-12 rad), so the marks are a superset and the FP64 test alone decides.
 // Marking with an FP64 dot product per pair and lane took half of the
 // kernel's vector instructions (47.2 million samples x 2 onto nside 512: 3.74
 // ms, 3.35 with these marks and the kernel type fixed at compile time, and
@@ -93,9 +95,9 @@ __global__ void __launch_bounds__(64 * KW, CMAX <= 4 && KT != 3 && SHORT ? 5 : 4
     float smax = s;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) smax = fmaxf(smax, __shfl_xor(smax, o, 64));
-    const float cs2 = (float)kp.cs2;
-    const float ext = sqrtf(smax) + sqrtf(cs2);
-    const float lim = cs2 * (1.0f + 1e-6f) + 4e-6f * ext * ext + 1e-30f;
+    const float reach = sqrtf((float)kp.cs2) + 2e-15f;
+    const float ext = sqrtf(smax) + reach;
+    const float lim = reach * reach * (1.0f + 1e-6f) + 4e-6f * ext * ext;
     const float c0 = -2.0f * u, c1 = -2.0f * v, c3 = ok ? s - lim : 1e30f;
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
