@@ -211,6 +211,25 @@ __global__ void __launch_bounds__(64 * CWV * KW, 2) k_gather_wide(
       }
     }
   };
+  // FP64 rows become FP32 once the products of the chunk before have covered
+  // their loads: as they are they would not fit beside the weights
+  constexpr bool WIDE_IN = sizeof(T) == 8;
+  float cv[WIDE_IN ? kWSteps : 1][4];
+  auto settle = [&]() {
+    if constexpr (WIDE_IN) {
+#pragma unroll
+      for (int i = 0; i < kWSteps; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          cv[i][j] = cvt_in<T>(raw[i][j]);
+          __asm__ volatile("" : "+v"(cv[i][j]));
+        }
+    }
+  };
+  auto val = [&](int i, int j) -> float {
+    if constexpr (WIDE_IN) return cv[i][j];
+    else return cvt_in<T>(raw[i][j]);
+  };
   float* const sd = reinterpret_cast<float*>(s_buf[wv]);
   // fetched block -> LDS; true when it holds a non-finite value
   auto stage = [&]() -> bool {
@@ -218,8 +237,8 @@ __global__ void __launch_bounds__(64 * CWV * KW, 2) k_gather_wide(
 #pragma unroll
     for (int i = 0; i < kWSteps; ++i) {
       float4 v;
-      v.x = cvt_in<T>(raw[i][0]); v.y = cvt_in<T>(raw[i][1]);
-      v.z = cvt_in<T>(raw[i][2]); v.w = cvt_in<T>(raw[i][3]);
+      v.x = val(i, 0); v.y = val(i, 1);
+      v.z = val(i, 2); v.w = val(i, 3);
       nf = fmaf(v.x, 0.0f, nf); nf = fmaf(v.y, 0.0f, nf);
       nf = fmaf(v.z, 0.0f, nf); nf = fmaf(v.w, 0.0f, nf);
       *reinterpret_cast<float4*>(sd + (4 * i + lk) * 64 + 4 * li) = v;
@@ -345,6 +364,7 @@ __global__ void __launch_bounds__(64 * CWV * KW, 2) k_gather_wide(
   __syncthreads();
   if (nloc > 0) {
     fetch(0);
+    settle();
     form(0, 0);
   }
   // record slots of chunks ch + 1, ch + 2 (a lone wavefront is done with the
@@ -367,7 +387,9 @@ __global__ void __launch_bounds__(64 * CWV * KW, 2) k_gather_wide(
       load_rec(ch + (NR > 1 ? 3 : 2));
     }
     if (CWV == 1) wave_lds_order();
-    if (ch + 1 < nloc) fetch(r1);
+    // (FP64 rows: also past the last chunk, as rows of zeros and empty lists, so
+    // that no register is kept for a chunk without them)
+    if (WIDE_IN || ch + 1 < nloc) fetch(r1);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const int nst = __builtin_amdgcn_readfirstlane(s_nst[buf][kw][g]);
@@ -391,7 +413,8 @@ __global__ void __launch_bounds__(64 * CWV * KW, 2) k_gather_wide(
         acc[g][3] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, v3, acc[g][3], 0, 0, 0);
       }
     }
-    if (ch + 1 < nloc) form(r1, NB > 1 ? buf ^ 1 : 0);
+    settle();
+    if (WIDE_IN || ch + 1 < nloc) form(r1, NB > 1 ? buf ^ 1 : 0);
     if (NR > 1) {
       r1 = r2;
       r2 = r2 == 2 ? 0 : r2 + 1;
@@ -420,6 +443,7 @@ __global__ void __launch_bounds__(64 * CWV * KW, 2) k_gather_wide(
       else wave_lds_order();
       form(0, 0);
       fetch(0);
+      settle();
       const bool mine = stage();
       if (CWV > 1) __syncthreads();
       else wave_lds_order();
