@@ -64,8 +64,14 @@ static void launch_dt(const TileView& tv, const KernelParams& kp, const void* da
   // Up to 64 channels a workgroup of four wavefronts still beats two, although
   // half of them have no channels: they share the weights (48 channels: 283
   // us against 331 with two wavefronts and one step, 344 with two steps).
-  if (nchan <= 128) launch_cfg<4, 1, MODE, T, 2>(tv, kp, data, zrow, ld, nchan, ov, st);
-  else if (nchan <= 256) launch_cfg<8, 1, MODE, T, 2>(tv, kp, data, zrow, ld, nchan, ov, st);
+  // FP64 rows take one step per stage up to 256 channels: within the 128
+  // registers of four wavefronts on a SIMD two steps spill in every kernel
+  // but the circular Gaussian of short supports (120,000 samples x 200
+  // channels onto 200 x 200, elliptical: 227 us against 427; x 100, FP16: 167
+  // against 222; the largest loss is 10 %, at 256 channels of BF16 mode).
+  constexpr int KS = sizeof(T) == 8 ? 1 : 2;
+  if (nchan <= 128) launch_cfg<4, 1, MODE, T, KS>(tv, kp, data, zrow, ld, nchan, ov, st);
+  else if (nchan <= 256) launch_cfg<8, 1, MODE, T, KS>(tv, kp, data, zrow, ld, nchan, ov, st);
   else if (nchan <= 512) launch_cfg<8, 2, MODE, T, 2>(tv, kp, data, zrow, ld, nchan, ov, st);
   else launch_cfg<8, 4, MODE, T, 1>(tv, kp, data, zrow, ld, nchan, ov, st);
 }

@@ -392,12 +392,11 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
   // this lane's A-operand values (raw input) of one chunk
   // 16-bit input of the operand's own type is used bit for bit; any other input is converted through FP32.
   constexpr bool DIRECT = (BF16IN && !F16) || (std::is_same<T, _Float16>::value && F16);
-  // (held as delivered until they are used: a conversion at the load would
-  // wait for it; but four blocks of FP64 values do not fit the registers)
+  // (16-bit and FP32 values are held as delivered until they are used: a
+  // conversion at the load would wait for it.  FP64 values become FP32 at the
+  // load all the same: 16 or 32 more registers spilled)
   constexpr bool RAW16 = sizeof(T) == 2;
-  constexpr bool RAW64 = sizeof(T) == 8 && BPW * KS <= 2;
-  using raw_t = typename std::conditional<RAW16, uint32_t,
-                typename std::conditional<RAW64, double, float>::type>::type;
+  using raw_t = typename std::conditional<RAW16, uint32_t, float>::type;
   raw_t raw[BPW][KS][8];
   // Lanes whose channel lies past cend read the last valid channel of the
   // same row instead, so that every address stays inside the caller's row (or
@@ -414,8 +413,7 @@ __device__ __forceinline__ void mfma_tile(const TileView tv, const KernelParams 
           raw[b][s][i] = (uint32_t)ldg<GL>(reinterpret_cast<const uint16_t*>(data), rw[i] + cofs);
         } else {
           const T v = ldg<GL>(data, rw[i] + cofs);
-          if constexpr (RAW64) raw[b][s][i] = v;
-          else raw[b][s][i] = in_f32<T>(&v);
+          raw[b][s][i] = in_f32<T>(&v);
         }
       }
     }

@@ -63,3 +63,9 @@ def test_wide_gather_of_fp64_rows(spills):
         assert v <= 16, (k, v)
     for k, v in _forms(spills, r"13k_gather_wideILi4ELi1ELi3ELb[01]EdE").items():
         assert v <= 32, (k, v)
+
+
+def test_matrix_core_contraction_of_fp64_rows(spills):
+    """Up to 256 channels."""
+    for k, v in _forms(spills, r"13k_gather_mfmaILi[48]ELi1E.*EdLi\dEE").items():
+        assert v <= 16, (k, v)
