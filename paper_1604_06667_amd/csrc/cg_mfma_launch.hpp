@@ -27,9 +27,22 @@ static void launch_cfg(const TileView& tv, const KernelParams& kp, const void* d
                        const void* zrow, int64_t ld, int64_t nchan, const OutView& ov,
                        hipStream_t st) {
   constexpr int CP = NW * BPW * 32;
+  const bool full = nchan % CP == 0;
+  // Elliptical kernels of long supports, BF16 mode, more than 512 channels but
+  // no multiple of 1024: four blocks of accumulators, the bounds of a ragged
+  // range and the call for long chords leave 37 to 106 registers spilled in
+  // the loop, two blocks none, which pays for the weights' being formed twice
+  // (120,000 samples x 1000 channels onto 200 x 200: BF16 rows 1125 us with
+  // four and 449 with two, FP16 620 and 477, FP32 712 and 502; 43,200 x 600:
+  // 277 and 217, 222 and 225, 238 and 222).  Whole multiples of 1024 spill
+  // 23 and are the faster so (BF16 rows 157 and 191 us, 30,000 samples).
+  constexpr bool RAGGED2 = BPW == 4 && MODE == 0 && sizeof(T) <= 4;
+  if constexpr (RAGGED2) {
+    if (!full && kp.type == 1 && !short_support(kp))
+      return launch_cfg<8, 2, MODE, T, 2>(tv, kp, data, zrow, ld, nchan, ov, st);
+  }
   const int64_t npass = (nchan + CP - 1) / CP;
   const dim3 g((unsigned)(tv.ntiles * npass)), b(NW * 64);
-  const bool full = nchan % CP == 0;
   const T* d = (const T*)data;
   const T* z = (const T*)zrow;
   const bool sh = short_support(kp);
@@ -38,7 +51,7 @@ static void launch_cfg(const TileView& tv, const KernelParams& kp, const void* d
     if (full)                                                                                   \
       hipLaunchKernelGGL((k_gather_mfma<NW, BPW, KT_, SH_, MODE, true, T, KS>), g, b, 0, st, tv, kp, \
                          d, z, ld, nchan, ov);                                                  \
-    else                                                                                        \
+    else if constexpr (!(RAGGED2 && KT_ == 1 && !SH_))                                          \
       hipLaunchKernelGGL((k_gather_mfma<NW, BPW, KT_, SH_, MODE, false, T, KS>), g, b, 0, st, tv, kp, \
                          d, z, ld, nchan, ov);                                                  \
   } while (0)

@@ -69,3 +69,10 @@ def test_matrix_core_contraction_of_fp64_rows(spills):
     """Up to 256 channels."""
     for k, v in _forms(spills, r"13k_gather_mfmaILi[48]ELi1E.*EdLi\dEE").items():
         assert v <= 16, (k, v)
+
+
+def test_ragged_channels_under_a_long_ellipse(spills):
+    """More than 512 channels, BF16 mode, elliptical kernel, support above 0.57 deg."""
+    assert not [k for k in spills if re.search(r"13k_gather_mfmaILi8ELi4ELi1ELb0ELi0ELb0E(f|t|DF16_)Li", k)]
+    for k, v in _forms(spills, r"13k_gather_mfmaILi8ELi2ELi1ELb0ELi0ELb0E(f|t|DF16_)Li").items():
+        assert v == 0, (k, v)
