@@ -37,8 +37,9 @@ struct cg_batch {
   std::vector<int64_t> items_for_n;          // sample counts the queue was ordered for
   // tuned launch shape (cg::launch_batch_mfma), item width, workgroups per CU
   // (untuned: 256 channels per item, four wavefronts of two channel blocks,
-  // the tuner's choice on all of four batches of 6 to 16 jobs; the largest
-  // takes 3.0 ms so, 3.4 with eight wavefronts of one block and 3.5 of two)
+  // the tuner's choice on each of five batches of 6 to 16 jobs, of BF16 and of
+  // FP32 rows; the contraction of the largest, BF16, takes 2.5 ms so, 3.4 with
+  // one block, and with eight wavefronts 3.3 of one block and 3.0 of two)
   int shape = 3, split = 0, bpc = 0;
   int form = cg::BATCH_ANY;                  // kernel form of the uploaded job table
   // graph: the pass over cap_in, with a job table and offsets of its own that

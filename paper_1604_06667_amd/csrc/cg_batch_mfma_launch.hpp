@@ -10,11 +10,15 @@ namespace cg {
 //   shape 0: 8 x 1 (256 channels per item)    shape 1: 8 x 2 (512)
 //   shape 2: 4 x 1 (128)                      shape 3: 4 x 2 (256, two workgroups per CU)
 // Two 16-sample steps per pipeline stage, as in the per-grid kernel (16 jobs:
-// 3.2 ms with one step, 2.9 with two; shape 3).
+// 3.2 ms with one step, 2.9 with two; shape 3), one for FP64 rows, whose
+// second step spills (16 jobs 2.77 ms with two and 2.05 with one in shape 3,
+// another 16 4.10 and 3.81).
 // (4-wavefront workgroups are held to two wavefronts per SIMD, so that two
-// of them share a compute unit and cover each other's barrier waits)
+// of them share a compute unit and cover each other's barrier waits.  Shape 0
+// has no such bound: at four per SIMD it spilled 27 to 143 registers, 16 jobs
+// of FP32 rows 2.74 against 2.11 ms, BF16 2.22 and 2.05)
 template <int NW, int BPW, int KT, bool SHORT, int MODE, typename T>
-__global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : BPW == 1 ? 4 : 1) k_batch_mfma(
+__global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_batch_mfma(
     const BatchJob* __restrict__ jobs, const BatchItem* __restrict__ items, BatchQueues q,
     int* counter, BatchRanges br, const T* __restrict__ zrow) {
   __shared__ int64_t s_item;
@@ -62,9 +66,10 @@ __global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : BPW == 1 ? 4 : 1) k_bat
     ov.cst = jb.cst;
     ov.tst = jb.tst;
     ov.mode = ACC_FINAL;
-    mfma_tile<NW, BPW, KT, SHORT, MODE, false, T, 2, true>(tv, jb.kp, (const T*)jb.data, zrow,
-                                                           jb.ld, jb.nchan, ov, item.tile,
-                                                           item.c0, item.cend);
+    constexpr int KS = sizeof(T) == 8 ? 1 : 2;
+    mfma_tile<NW, BPW, KT, SHORT, MODE, false, T, KS, true>(tv, jb.kp, (const T*)jb.data, zrow,
+                                                            jb.ld, jb.nchan, ov, item.tile,
+                                                            item.c0, item.cend);
   }
 }
 

@@ -76,3 +76,11 @@ def test_ragged_channels_under_a_long_ellipse(spills):
     assert not [k for k in spills if re.search(r"13k_gather_mfmaILi8ELi4ELi1ELb0ELi0ELb0E(f|t|DF16_)Li", k)]
     for k, v in _forms(spills, r"13k_gather_mfmaILi8ELi2ELi1ELb0ELi0ELb0E(f|t|DF16_)Li").items():
         assert v == 0, (k, v)
+
+
+def test_batch_contraction(spills):
+    """Eight wavefronts of one block, and FP64 rows in every shape."""
+    for k, v in _forms(spills, r"12k_batch_mfmaILi8ELi1E").items():
+        assert v == 0, (k, v)
+    for k, v in _forms(spills, r"12k_batch_mfmaILi\dELi\d.*EdEE").items():
+        assert v == 0, (k, v)
