@@ -7,6 +7,11 @@ using namespace cgh;
 
 bool small_c(const cg_gridder* g) { return g->nchan <= cg::kSmallC && g->prec == CG_PREC_FP32; }
 
+// Channels whose rows a grid call sorts into its workspace.
+int64_t row_chan(const cg_gridder* g) {
+  return small_c(g) && g->nchan > cg::kRecC ? g->nchan : 0;
+}
+
 // The targets cover at least an eighth of the sky (a WCS grid's nominal area,
 // a HEALPix map's all of it; a list of sight lines is not known to).
 bool wide_sky(const cg_gridder* g) {
@@ -145,9 +150,9 @@ cg_status run_lookup(cg_gridder* g, const double* lon, const double* lat, int64_
   cg_status s = ensure_span(g, st);
   if (s != CG_OK) return s;
   const int64_t nside = g->nside;
-  workspace_layout(n, nside, with_data ? g->nchan : 0, base, &g->ws);
+  workspace_layout(n, nside, with_data ? row_chan(g) : 0, base, &g->ws);
   Workspace& w = g->ws;
-  const int npack = with_data && g->nchan <= 2 ? (int)g->nchan : 0;
+  const int npack = with_data && g->nchan <= cg::kRecC ? (int)g->nchan : 0;
   CG_HIP(cg::launch_prep(lon, lat, n, nside, w.keys, g->flag.as<int>(), w.rec, data,
                          dtype, ld, npack, st),
          "prep");
@@ -197,7 +202,7 @@ cg::TileView tile_view(const cg_gridder* g) {
 
 // Workspace bytes of a grid call on n samples with the handle's settings.
 size_t ws_bytes_for(const cg_gridder* g, int64_t n) {
-  return workspace_layout(n, g->nside, small_c(g) ? g->nchan : 0, nullptr, nullptr);
+  return workspace_layout(n, g->nside, row_chan(g), nullptr, nullptr);
 }
 
 // The workspace of a grid call: the caller's (checked for size and

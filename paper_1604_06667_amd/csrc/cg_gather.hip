@@ -155,7 +155,7 @@ __global__ void __launch_bounds__(64 * KW, CMAX <= 4 && KT != 3 && SHORT ? 5 : 4
       lr = tv.srec[pos];
       // every slot of the row is set (zeros past nchan), so the walk reads
       // and multiplies all CMAX slots without a branch per channel
-      if constexpr (CMAX <= 2) {   // carried in the record
+      if constexpr (CMAX <= kRecC) {   // carried in the record
         const uint64_t d = (uint64_t)__double_as_longlong(lr.w);
         ld[0] = __uint_as_float((uint32_t)d);
         if (CMAX > 1) ld[CMAX - 1] = __uint_as_float((uint32_t)(d >> 32));

@@ -150,7 +150,7 @@ inline int bits_for(uint64_t v) {
 // caller's or the handle's own): HEALPix keys and sample indices with their
 // sort buffers and histogram, the ring offsets, the per-sample records of
 // the prep step (input order) and of the sorted samples (unit vector and
-// input row) and, for narrow FP32 grids, the sorted data rows.  Every piece
+// input row) and, for FP32 grids of 3 to 16 channels, the sorted data rows.  Every piece
 // starts on a 256-byte boundary.
 struct Workspace {
   uint32_t *keys = nullptr, *vals = nullptr, *keys2 = nullptr, *vals2 = nullptr;

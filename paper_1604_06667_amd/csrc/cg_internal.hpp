@@ -12,6 +12,7 @@ namespace cg {
 
 constexpr int kTile = 64;              // targets per tile (one wavefront of target slots)
 constexpr int kSmallC = 16;            // up to this many channels the FP32 path stages sorted rows
+constexpr int kRecC = 2;                // of those, this many travel in the sorted records instead
 constexpr int kSortThreads = 512;
 
 // Kernel constants derived on the host by set_kernel.
