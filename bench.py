@@ -76,9 +76,11 @@ def header_of(wcs, nchan):
 # Sources that define each counted kernel (with the headers every kernel
 # includes): a change elsewhere in the library leaves its counters valid.
 COUNTED_SOURCES = {
-    "contraction_bf16": ["cg_mfma.hip", "cg_mfma_launch.hpp", "cg_mfma_tile.hpp"],
-    "contraction_sightlines_bf16": ["cg_mfma.hip", "cg_mfma_launch.hpp", "cg_mfma_tile.hpp"],
-    "contraction_batched_bf16": ["cg_batch_mfma.hip", "cg_batch_mfma_launch.hpp", "cg_mfma_tile.hpp"],
+    "contraction_bf16": ["cg_mfma.hip", "cg_mfma_f32.hip", "cg_mfma_launch.hpp", "cg_mfma_tile.hpp"],
+    "contraction_sightlines_bf16": ["cg_mfma.hip", "cg_mfma_bf16.hip", "cg_mfma_launch.hpp",
+                                    "cg_mfma_tile.hpp"],
+    "contraction_batched_bf16": ["cg_batch_mfma.hip", "cg_batch_mfma_bf16.hip",
+                                 "cg_batch_mfma_launch.hpp", "cg_mfma_tile.hpp"],
 }
 COMMON_SOURCES = ["cg_internal.hpp", "healpix.hpp", "wcs.hpp"]
 

@@ -6,8 +6,9 @@
 // outputs are owned by one workgroup, so no atomics are needed (the
 // ownership argument of Sect. 2.2).  The support test is FP64 on unit
 // vectors; weights are FP32; products and sums are FP64 (an FP32 weight
-// times an FP32 value is exact in FP64), so the result does not depend on
-// the order in which candidates arrive, even where the sums cancel.
+// times an FP32 value is exact in FP64), so the order in which candidates
+// arrive, and the number of wavefronts that share a tile, change a sum only
+// by its rounding in FP64.
 #include "cg_internal.hpp"
 
 namespace cg {
@@ -77,7 +78,9 @@ __global__ void __launch_bounds__(64 * KW, CMAX <= 4 && KT != 3 && SHORT ? 5 : 4
   double wacc = 0.0;
   const uint32_t nr = tv.nr[tile];
   const uint32_t* rng = tv.rng + 2 * tv.roff[tile];   // per range: first sorted position, first candidate index
-  // axes e, f perpendicular to the first valid target of the tile, c
+  // axes e, f perpendicular to the first valid target of the tile, c (the
+  // branch-free basis of Duff et al. 2017, "Building an Orthonormal Basis,
+  // Revisited")
   const uint64_t valid = __ballot(isfinite(tx));
   const int first = valid ? __builtin_ctzll(valid) : 0;
   const double cx = __shfl(tx, first, 64), cy = __shfl(ty, first, 64), cz = __shfl(tz, first, 64);

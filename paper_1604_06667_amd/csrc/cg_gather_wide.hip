@@ -6,9 +6,9 @@
 // FP64, and products and sums are FP64 (v_mfma_f64_16x16x4): targets as M,
 // channels as N, candidate samples as K.
 //
-// What bounds it: the FP64 rate (matrix and vector FP64 share it, 47-60
-// TFLOP/s in a loop of nothing else), so the products spent on pairs outside
-// the support are what counts.  The tile's 64 targets are therefore taken as
+// What bounds it: the FP64 rate (matrix and vector FP64 share it; a large
+// library product reaches 71 TFLOP/s, a loop of vector FMAs 57), so the
+// products spent on pairs outside the support are what counts.  The tile's 64 targets are therefore taken as
 // four groups of 16 (4 x 4 pixels of a WCS tile, else 16 consecutive slots)
 // and each group's products run over a list of its own: the candidates
 // within the support of the group's bounding cap, about half of the tile's

@@ -3,12 +3,12 @@
 // For one tile of 64 targets, Eq. (1) over a chunk of candidate samples
 // is a dense product S[c][t] += sum_k R[k][c] w[t][k] (the paper's remark
 // that all channels of a spectrum share one weight, Sect. 5, is what makes
-// it a GEMM).  The weight block w[64][32] is computed once per chunk (FP64
-// support test and distance, FP32 kernel value, rounded to BF16/FP16) and
-// shared by all channel blocks; each lane loads the data values of its own
-// operand of v_mfma_f32_32x32x16_{bf16,f16} (channels as M, targets as N,
-// samples as K) and converts them to BF16/FP16 in registers.  Accumulation is FP32 in the matrix cores.  In BF16 mode data and
-// weights are each split into a BF16 high part and a BF16 residual and the
+// it a GEMM).  The weight block w[64][16 KS] of a chunk of KS 16-sample steps
+// is computed once (FP64 support test and distance, FP32 kernel value, rounded
+// to BF16/FP16) and shared by all channel blocks; each lane loads the data
+// values of its own operand of v_mfma_f32_32x32x16_{bf16,f16} (channels as M,
+// targets as N, samples as K) and converts them to BF16/FP16 in registers.
+// Accumulation is FP32 in the matrix cores.  In BF16 mode data and weights are each split into a BF16 high part and a BF16 residual and the
 // block is formed from three products (hi*hi + lo*hi + hi*lo); a single
 // BF16 product would round data and weights to 2^-9, which is too coarse
 // for the 2e-3 bound on noise-dominated channels.  Two weight sums are kept

@@ -68,27 +68,6 @@ __device__ __forceinline__ float in_f32<uint16_t>(const uint16_t* p) {
 template <>
 __device__ __forceinline__ float in_f32<_Float16>(const _Float16* p) { return (float)*p; }
 
-// 4 consecutive channels of one row as floats (zeros past nvalid).
-template <typename T>
-__device__ __forceinline__ void load4(const T* __restrict__ p, int nvalid, bool vec_ok, float* o) {
-  if (vec_ok && nvalid >= 4) {
-    if constexpr (sizeof(T) == 4) {
-      const float4 v = *reinterpret_cast<const float4*>(p);
-      o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w;
-      return;
-    } else if constexpr (sizeof(T) == 2) {
-      const uint2 v = *reinterpret_cast<const uint2*>(p);
-      const uint16_t h[4] = {(uint16_t)(v.x & 0xffff), (uint16_t)(v.x >> 16),
-                             (uint16_t)(v.y & 0xffff), (uint16_t)(v.y >> 16)};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) o[i] = in_f32<T>(reinterpret_cast<const T*>(&h[i]));
-      return;
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i) o[i] = (i < nvalid) ? in_f32<T>(p + i) : 0.0f;
-}
-
 // MODE 0: BF16 with hi/lo split of data and weights, three products per
 //         block (hi*hi + lo*hi + hi*lo);
 // MODE 1: FP16, one product per block.
