@@ -22,7 +22,7 @@ struct cg_batch {
   std::vector<int64_t> noff;                 // sample offsets, size njobs + 1
   int64_t ntot = 0;
   std::vector<cg::BatchJob> hjobs;           // host copy of the job table
-  cg::BatchJob* pin_jobs = nullptr;          // pinned staging of the job table, then of the captured one
+  cg::BatchJob* pin_jobs = nullptr;          // pinned staging of the job table
   int64_t* pin_off = nullptr;                // pinned staging of noff | toff | rooff
   uint64_t* pin_word = nullptr;
   DevBuf d_jobs, d_off, keys, vals, keys2, vals2, hist, ring_off, sx, ranges, nranges, ncand,
@@ -47,7 +47,8 @@ struct cg_batch {
   std::vector<cg_batch_job> cap_in;
   std::vector<cg::BatchJob> cap_hjobs;
   std::vector<int64_t> cap_noff;
-  DevBuf cap_jobs, cap_off;
+  DevBuf cap_jobs, cap_off;                  // (from the first capture on)
+  cg::BatchJob* pin_cap = nullptr;           // pinned staging of cap_jobs
   int graph_form = cg::BATCH_ANY;
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
@@ -347,7 +348,7 @@ cg_status size_pass(cg_batch* b) {
   if ((s = grow(b, b->vals, 4 * n, "alloc keys")) != CG_OK) return s;
   if ((s = grow(b, b->keys2, 4 * n, "alloc keys")) != CG_OK) return s;
   if ((s = grow(b, b->vals2, 4 * n, "alloc keys")) != CG_OK) return s;
-  if ((s = grow(b, b->hist, 4 * cg::radix_hist_elems(n), "alloc hist")) != CG_OK) return s;
+  if ((s = grow(b, b->hist, 4 * cg::radix_hist_elems_of(n), "alloc hist")) != CG_OK) return s;
   if ((s = grow(b, b->sx, 32 * n, "alloc sorted records")) != CG_OK) return s;
   return CG_OK;
 }
@@ -399,9 +400,8 @@ cg_status follow_gridders(cg_batch* b, hipStream_t st) {
   const size_t bytes = sizeof(cg::BatchJob) * now.size();
   if (memcmp(now.data(), b->cap_hjobs.data(), bytes) != 0) {
     b->cap_hjobs = now;
-    cg::BatchJob* pin = b->pin_jobs + now.size();   // (upload_tables has waited for `st`)
-    memcpy(pin, now.data(), bytes);
-    CG_HIP(hipMemcpyAsync(b->cap_jobs.p, pin, bytes, hipMemcpyHostToDevice, st),
+    memcpy(b->pin_cap, now.data(), bytes);   // (upload_tables has waited for `st`)
+    CG_HIP(hipMemcpyAsync(b->cap_jobs.p, b->pin_cap, bytes, hipMemcpyHostToDevice, st),
            "upload captured jobs");
   }
   if (b->form <= b->graph_form) return CG_OK;
@@ -483,8 +483,6 @@ cg_status cg_batch_create(cg_batch** out, cg_gridder* const* jobs, int32_t njobs
   const Allocator& al = b->alloc;
   if ((e = ensure(al, b->d_jobs, sizeof(cg::BatchJob) * njobs)) != hipSuccess ||
       (e = ensure(al, b->d_off, sizeof(int64_t) * 3 * (njobs + 1))) != hipSuccess ||
-      (e = ensure(al, b->cap_jobs, sizeof(cg::BatchJob) * njobs)) != hipSuccess ||
-      (e = ensure(al, b->cap_off, sizeof(int64_t) * 3 * (njobs + 1))) != hipSuccess ||
       (e = ensure(al, b->ring_off, 4 * std::max<int64_t>(b->nro, 1))) != hipSuccess ||
       (e = ensure(al, b->ranges, 8 * std::max<int64_t>(b->nranges_tot, 1))) != hipSuccess ||
       (e = ensure(al, b->nranges, 4 * nt)) != hipSuccess ||
@@ -495,7 +493,7 @@ cg_status cg_batch_create(cg_batch** out, cg_gridder* const* jobs, int32_t njobs
   if ((e = hipMemset(b->zrow.p, 0, 8 * 512)) != hipSuccess ||
       (e = hipMemset(b->flags.p, 0, 64)) != hipSuccess)
     return done(hip_fail(e, "clear batch"));
-  if ((e = hipHostMalloc((void**)&b->pin_jobs, sizeof(cg::BatchJob) * 2 * njobs,
+  if ((e = hipHostMalloc((void**)&b->pin_jobs, sizeof(cg::BatchJob) * njobs,
                          hipHostMallocDefault)) != hipSuccess ||
       (e = hipHostMalloc((void**)&b->pin_off, sizeof(int64_t) * 3 * (njobs + 1),
                          hipHostMallocDefault)) != hipSuccess ||
@@ -584,9 +582,19 @@ cg_status cg_batch_capture(cg_batch* b, const cg_batch_job* in, void* stream) {
   CG_HIP(hipSetDevice(b->device), "hipSetDevice");
   hipStream_t st = (hipStream_t)stream;
   drop_graph(b);
+  const size_t njobs = b->jobs.size();
+  CG_HIP(ensure(b->alloc, b->cap_jobs, sizeof(cg::BatchJob) * njobs), "alloc captured jobs");
+  CG_HIP(ensure(b->alloc, b->cap_off, sizeof(int64_t) * 3 * (njobs + 1)), "alloc captured jobs");
+  if (!b->pin_cap)
+    CG_HIP(hipHostMalloc((void**)&b->pin_cap, sizeof(cg::BatchJob) * njobs, hipHostMallocDefault),
+           "pinned captured jobs");
+  // (sort scratch for passes of fewer samples too, which may need more of it)
+  int64_t ntot = 0;
+  for (size_t j = 0; j < njobs; ++j) ntot += in[j].nsamples;
+  if ((s = grow(b, b->hist, 4 * cg::radix_hist_elems(std::max<int64_t>(ntot, 1)), "alloc hist")) != CG_OK)
+    return s;
   if ((s = eager_pass(b, in, st)) != CG_OK) return s;
   // the pass's own tables, for the graph alone
-  const size_t njobs = b->jobs.size();
   CG_HIP(hipMemcpyAsync(b->cap_jobs.p, b->d_jobs.p, sizeof(cg::BatchJob) * njobs,
                         hipMemcpyDeviceToDevice, st),
          "copy jobs");
@@ -704,6 +712,7 @@ void cg_batch_destroy(cg_batch* b) {
   for (DevBuf* d : bufs) d->release();
   if (b->pin_jobs) (void)hipHostFree(b->pin_jobs);
   if (b->pin_off) (void)hipHostFree(b->pin_off);
+  if (b->pin_cap) (void)hipHostFree(b->pin_cap);
   if (b->pin_word) (void)hipHostFree(b->pin_word);
   if (b->pin_items) (void)hipHostFree(b->pin_items);
   delete b;

@@ -15,10 +15,12 @@ namespace cg {
 // another 16 4.10 and 3.81).
 // (4-wavefront workgroups are held to two wavefronts per SIMD, so that two
 // of them share a compute unit and cover each other's barrier waits.  Shape 0
-// has no such bound: at four per SIMD it spilled 27 to 143 registers, 16 jobs
-// of FP32 rows 2.74 against 2.11 ms, BF16 2.22 and 2.05)
+// with 16-bit rows is held to four: it spills 27 to 62 registers for it, at
+// even times (five batches 1.05, 2.22, 0.91, 0.94 and 3.22 ms against 1.10,
+// 2.05, 0.97, 0.83 and 3.25); FP32 rows take 2.74 ms with the bound and 2.11
+// without, FP64 rows 4.08 and 2.61)
 template <int NW, int BPW, int KT, bool SHORT, int MODE, typename T>
-__global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) k_batch_mfma(
+__global__ void __launch_bounds__(NW * 64, NW == 4 ? 2 : BPW == 1 && sizeof(T) == 2 ? 4 : 1) k_batch_mfma(
     const BatchJob* __restrict__ jobs, const BatchItem* __restrict__ items, BatchQueues q,
     int* counter, BatchRanges br, const T* __restrict__ zrow) {
   __shared__ int64_t s_item;

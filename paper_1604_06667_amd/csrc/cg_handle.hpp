@@ -176,7 +176,7 @@ inline size_t workspace_layout(int64_t n, int64_t nside, int64_t sdata_chan, cha
   ws.vals2 = (uint32_t*)take(4 * un);
   ws.ring_off = (uint32_t*)take(4 * (size_t)(4 * nside + 1));
   // (the sort's histograms are done with before the sorted records are written)
-  const size_t hist = 4 * cg::radix_hist_elems((int64_t)un), srec = 32 * un;
+  const size_t hist = 4 * cg::radix_hist_elems_of((int64_t)un), srec = 32 * un;
   ws.srec = (double*)take(hist > srec ? hist : srec);
   ws.hist = (uint32_t*)ws.srec;
   ws.rec = (double*)take(32 * un);

@@ -364,7 +364,9 @@ hipError_t launch_prep(const double* lon, const double* lat, int64_t n, int64_t 
 hipError_t radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_tmp, uint32_t* vals_tmp,
                       uint32_t* hist, int64_t n, int bits, bool iota, bool* result_in_tmp,
                       hipStream_t st);
-size_t radix_hist_elems(int64_t n);   // histogram and digit totals of a sort of up to n pairs
+// histogram and digit totals of a sort of n pairs, and of any sort of up to n
+size_t radix_hist_elems_of(int64_t n);
+size_t radix_hist_elems(int64_t n);
 // ring offsets and the permutation of the sorted samples:
 // srec: one record per sorted sample (unit vector; input row as int64 bits, or
 // with data and npack > 0 the channels 0-1 as FP32); sdata: the rows of narrow

@@ -442,16 +442,20 @@ static int sort_items(int64_t n) {
   return n <= kSortBlocks * 4 * kSortThreads ? 4 : n <= kSortBlocks * 8 * kSortThreads ? 8 : 16;
 }
 
-// For n pairs or fewer: a sort of fewer pairs may have more blocks, but with
-// less than 16 pairs per thread never more than kSortBlocks, nor more than n
-// pairs make with 4.
-size_t radix_hist_elems(int64_t n) {
-  const int64_t tile = (int64_t)kSortThreads * sort_items(n), least = 4 * (int64_t)kSortThreads;
-  int64_t nb = (n + tile - 1) / tile;
-  int64_t below = (n + least - 1) / least;
-  if (below > kSortBlocks) below = kSortBlocks;
-  if (nb < below) nb = below;
+size_t radix_hist_elems_of(int64_t n) {
+  const int64_t tile = (int64_t)kSortThreads * sort_items(n);
+  const int64_t nb = (n + tile - 1) / tile;
   return ((size_t)(nb < 1 ? 1 : nb) + 1) << kDigitBits;
+}
+
+// A sort of fewer pairs may have more blocks, but with less than 16 pairs per
+// thread never more than kSortBlocks, nor more than n pairs make with 4.
+size_t radix_hist_elems(int64_t n) {
+  const int64_t least = 4 * (int64_t)kSortThreads;
+  int64_t nb = (n + least - 1) / least;
+  if (nb > kSortBlocks) nb = kSortBlocks;
+  const size_t own = radix_hist_elems_of(n), below = ((size_t)(nb < 1 ? 1 : nb) + 1) << kDigitBits;
+  return own > below ? own : below;
 }
 
 template <bool JOB, int NBITS, int ITEMS>
