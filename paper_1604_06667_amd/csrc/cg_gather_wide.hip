@@ -16,7 +16,7 @@
 // support, against 27 % of the tile's).  The weights are formed for listed
 // pairs only, by one wavefront per group, and shared by all channels of the
 // workgroup through LDS.  The cube of 1e6 samples x 1024 channels onto 600 x
-// 600 pixels takes 8.7 ms (44 % of the SIMD cycles on the matrix cores, 23 %
+// 600 pixels takes 8.7 ms (44 % of the SIMD cycles on the matrix cores, 26 %
 // on vector instructions); one lane per channel with a readlane per pair, the
 // vector form of the same sums, took 21.8 ms.
 //
